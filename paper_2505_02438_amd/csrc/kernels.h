@@ -94,6 +94,17 @@ struct BwdParams {
     double lam, mu;
 };
 
+// backward on the plan's node groups (no group's rows are read twice)
+struct BwdGroupParams {
+    AsmParams A;           // the plan, geometry, densities and material (K unused)
+    const double *Kbar;
+    const uint8_t *mask;   // or null
+    const int32_t *cells;
+    double *part;          // [nen][n_cells]: part(e, i) by plan column
+    uint32_t *fixed;       // [n_cells] by plan column: the element's fixed dofs (with a mask)
+    void *drho;
+};
+
 // fuse: the whole step (Dirichlet table, energies, dc, compliance partials)
 hipError_t launch_assemble(int elem, int prec, const AsmParams &P, int64_t ngroups, hipStream_t st, bool fuse = false);
 // which assembly kernel launch_assemble runs: -1 = chosen by the plan's shape
@@ -128,6 +139,7 @@ hipError_t launch_cg_p_fused(double *p, const double *z, const double *part, int
 hipError_t launch_cg_p(double *p, const double *z, const double *sc, int64_t n, hipStream_t st);
 hipError_t launch_cg_scalars(int what, const double *part, int n, double *sc, hipStream_t st);
 hipError_t launch_backward(int elem, int prec, const BwdParams &P, hipStream_t st);
+hipError_t launch_backward_group(int elem, int prec, const BwdGroupParams &P, int64_t ngroups, hipStream_t st);
 
 // per-quadrature-point assembly (non-affine Q1): element blocks, then a
 // gather of every CSR block's contributions in ascending element order

@@ -21,6 +21,7 @@
 #include <map>
 #include <atomic>
 #include <mutex>
+#include <tuple>
 
 #include "block_sum.h"
 #include "internal.h"
@@ -1992,7 +1993,293 @@ __global__ __launch_bounds__(256) void k_backward(BwdParams P) {
     store_out<PREC>(P.drho, e, dE * det * acc);
 }
 
+// The same sums with every row of Kbar read once, on the assembly plan's node
+// groups.  k_backward's thread per element gathers 24-byte pieces of 24 rows
+// whose lines its neighbours need too: on the 120x40x40 hexahedra those
+// gathers move about 7 GB through L2 and take 1,098 us, where Kbar is 380 MB.
+// Here one workgroup per node group copies its nodes' row blocks to LDS in
+// whole runs, then lane (node, half of the element's nodes j) forms for each
+// element around the node
+//     part(e, i) = sum_j <X_ij, L(G^T M_ij G)>,  i = the node in e,
+// and k_backward_sum adds an element's NEN parts in order of i.  The parts
+// ([NEN][n_cells], 12 MB there) stay in the last-level cache.  Measured there:
+// 124 us in all (144 with every J^-1 full), 132 with a mask: 3.1 TB/s of Kbar.
+// What is left is latency: two workgroups per CU (62 KB of rows each), whose
+// loads, tables and sums follow each other.  Two workgroups per group with
+// half the rows each were slower (131 us), as were 8 values in flight per
+// thread instead of 16, and plain instead of non-temporal loads (both 140).
+// Lanes: N = 32, 16 or 8 nodes, 2 halves of j, and 64 / (2 N) elements k of
+// the node side by side where the group is small (P2 vertices: 24 elements,
+// at most 8 nodes).
+// MASK: entries in fixed rows or columns are constants of the assembly; each
+// element's fixed dofs (bit DIM i + a) are gathered once by k_backward_fixed
+// (a table of the group's blocks, from the neighbour lists and the mask, cost
+// 26 us there instead of 8).
+template <int DIM, int PREC, bool DIAG>
+__device__ __forceinline__ void backward_geometry(const AsmParams &A, int e, typename CT<PREC>::T (&G)[DIM][DIM]) {
+    using T = typename CT<PREC>::T;
+#pragma unroll
+    for (int m = 0; m < DIM; m++)
+#pragma unroll
+        for (int a = 0; a < DIM; a++)
+            G[m][a] = (DIAG && m != a) ? T(0) : (T)A.geo[(int64_t)(m * DIM + a) * A.n_cells + e];
+}
+
+template <int DIM, int NEN, int PREC, bool MASK, bool DIAG>
+__device__ __forceinline__ void backward_items(const BwdGroupParams &P, int nn, int deg, int blk, int K, int rkoff,
+                                               int eoff, const double *stage,
+                                               const typename CT<PREC>::T *sM, const uint16_t *tab,
+                                               const uint8_t *loc, const uint16_t *n2l, int w, int lane, int e, typename CT<PREC>::T (&G)[DIM][DIM]) {
+    using T = typename CT<PREC>::T;
+    constexpr int D2 = DIM * DIM, NG = kGroupNodes;
+    constexpr int kWaves = OsShape<DIM>::threads / 64;
+    const AsmParams &A = P.A;
+    const int64_t NC = A.n_cells;
+    const int lgN = nn > 16 ? 5 : nn > 8 ? 4 : 3;
+    const int node = lane & ((1 << lgN) - 1);
+    const int rest = lane >> lgN;            // 64 / N values: bit 0 the half of j, the others k
+    const int jh = rest & 1, ks = 32 >> lgN;  // elements of a node handled by one wave together
+    const int rl = DIM * deg;
+    const T lam = (T)A.lam, mu = (T)A.mu;
+    for (int k0 = w * ks; k0 < K; k0 += kWaves * ks) {
+        const int k = k0 + (rest >> 1);
+        const bool live = node < nn && k < K;
+        const int kk = live ? k : 0, nd = live ? node : 0;
+        if (k0 > w * ks) {
+            e = A.grp_elems[eoff + n2l[kk * NG + nd]];
+            backward_geometry<DIM, PREC, DIAG>(A, e, G);
+        }
+        const int i = loc[kk];
+        const uint32_t fx = MASK ? P.fixed[e] : 0;
+        // R[m][a] = sum_j sum_b (M_ij G)[m][b] L(X_ij)[a][b] (for a diagonal
+        // G: sum_j M_ij[m][a] L(X_ij)[m][a])
+        double R[DIM][DIM];
+#pragma unroll
+        for (int m = 0; m < DIM; m++)
+#pragma unroll
+            for (int a = 0; a < DIM; a++) R[m][a] = 0.0;
+        for (int j = jh; j < NEN; j += 2) {
+            const int p = tab[kk * NEN + j];
+            const int q = rkoff >= 0 ? (int)A.grp_rank[rkoff + p * NG + nd] : p;
+            const double *x = stage + nd * blk + DIM * q;
+            T X[DIM][DIM];
+#pragma unroll
+            for (int a = 0; a < DIM; a++)
+#pragma unroll
+                for (int b = 0; b < DIM; b++) X[a][b] = (T)x[a * rl + b];
+            if (MASK && fx) {
+                const uint32_t ri = fx >> (DIM * i), cj = fx >> (DIM * j);
+#pragma unroll
+                for (int a = 0; a < DIM; a++)
+#pragma unroll
+                    for (int b = 0; b < DIM; b++)
+                        if (((ri >> a) | (cj >> b)) & 1) X[a][b] = T(0);
+            }
+            T tr = 0;
+#pragma unroll
+            for (int a = 0; a < DIM; a++) tr += X[a][a];
+            T Y[DIM][DIM];
+#pragma unroll
+            for (int a = 0; a < DIM; a++)
+#pragma unroll
+                for (int b = 0; b < DIM; b++) Y[a][b] = lam * X[a][b] + mu * X[b][a] + (a == b ? mu * tr : T(0));
+            const T *M = sM + (i * NEN + j) * D2;
+            if (DIAG) {
+#pragma unroll
+                for (int m = 0; m < DIM; m++)
+#pragma unroll
+                    for (int a = 0; a < DIM; a++) R[m][a] += (double)(M[m * DIM + a] * Y[m][a]);
+            } else {
+#pragma unroll
+                for (int m = 0; m < DIM; m++) {
+                    T t[DIM];
+#pragma unroll
+                    for (int b = 0; b < DIM; b++) {
+                        T v = 0;
+#pragma unroll
+                        for (int n = 0; n < DIM; n++) v += M[m * DIM + n] * G[n][b];
+                        t[b] = v;
+                    }
+#pragma unroll
+                    for (int a = 0; a < DIM; a++) {
+                        T v = 0;
+#pragma unroll
+                        for (int b = 0; b < DIM; b++) v += t[b] * Y[a][b];
+                        R[m][a] += (double)v;
+                    }
+                }
+            }
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int m = 0; m < DIM; m++)
+#pragma unroll
+            for (int a = 0; a < DIM; a++) {
+                if (DIAG) s += (double)G[m][m] * (double)G[a][a] * R[m][a];
+                else s += (double)G[m][a] * R[m][a];
+            }
+        s += __shfl_xor(s, 1 << lgN);  // the other half of j
+        if (live && jh == 0) P.part[(int64_t)i * NC + e] = s;
+    }
+}
+
+template <int DIM, int NEN, int PREC, bool MASK>
+__global__ __launch_bounds__(OsShape<DIM>::threads) void k_backward_group(BwdGroupParams P) {
+    using T = typename CT<PREC>::T;
+    constexpr int kThreads = OsShape<DIM>::threads;
+    constexpr int D2 = DIM * DIM, NG = kGroupNodes;
+    const AsmParams &A = P.A;
+    extern __shared__ __align__(16) unsigned char smem[];
+    double *stage = reinterpret_cast<double *>(smem);                  // [A.stage]
+    T *sM = reinterpret_cast<T *>(stage + A.stage);                     // [NEN][NEN][D2]
+    int32_t *srows = reinterpret_cast<int32_t *>(sM + NEN * NEN * D2);  // [NG][2]
+    uint16_t *tab = reinterpret_cast<uint16_t *>(srows + NG * 2);       // [kmax][NEN]: position of node j of element k
+    uint8_t *loc = reinterpret_cast<uint8_t *>(tab + A.kmax * NEN);     // [kmax]: the node's own index in element k
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int w = wave_uniform(tid >> 6);
+    const int ngr = A.n_groups;
+    const int W = A.os_window;
+    const int bid = blockIdx.x;
+    const int base = bid - bid % W;
+    const int gg = base + W <= ngr ? base + (bid % 8) * (W / 8) + (bid - base) / 8 : bid;
+    if (gg >= ngr) return;
+    const int sg = wave_uniform(ldc(A.grp_info, kGrpInfo * gg + 0));
+    const int nn = wave_uniform(ldc(A.grp_info, kGrpInfo * gg + 1));
+    const int eoff = wave_uniform(ldc(A.grp_info, kGrpInfo * gg + 2));
+    const int n2off = wave_uniform(ldc(A.grp_info, kGrpInfo * gg + 4));
+    const int gflags = wave_uniform(ldc(A.grp_info, kGrpInfo * gg + 5));
+    const int K = wave_uniform(ldc(A.sig_info, 4 * sg + 0));
+    const int deg = wave_uniform(ldc(A.sig_info, 4 * sg + 1));
+    const int posoff = wave_uniform(ldc(A.sig_info, 4 * sg + 2));
+    const int blk = wave_uniform(ldc(A.sig_info, 4 * sg + 3));
+    const int rkoff = A.grp_rank_off ? wave_uniform(ldc(A.grp_rank_off, gg)) : -1;
+    if (tid < 2 * NG) srows[tid] = A.grp_rows[(int64_t)gg * 2 * NG + tid];
+    __syncthreads();
+    constexpr bool kMayDiag = NEN == (1 << DIM);
+    const bool diag = kMayDiag && (gflags & kGrpDiag);
+    // the lane's first element (backward_items' first step) and its geometry,
+    // read ahead of the rows
+    const int lgN = nn > 16 ? 5 : nn > 8 ? 4 : 3;
+    const int fk = w * (32 >> lgN) + (lane >> (lgN + 1)), fn = lane & ((1 << lgN) - 1);
+    const bool flive = fk < K && fn < nn;
+    const uint16_t *n2l = A.grp_n2l + n2off;
+    const int fe = A.grp_elems[eoff + n2l[flive ? fk * NG + fn : 0]];
+    T G[DIM][DIM];
+    if (diag) backward_geometry<DIM, PREC, true>(A, fe, G);
+    else backward_geometry<DIM, PREC, false>(A, fe, G);
+    // the group's row blocks, kLoads values per thread in flight together
+    constexpr int kLoads = 16;
+    const int bsz = D2 * deg, total = nn * bsz;
+    const int dn = kThreads / bsz, dof = kThreads % bsz;
+    int n = tid / bsz, o = tid % bsz;
+    for (int x0 = 0; x0 < total; x0 += kThreads * kLoads) {
+        double v[kLoads];
+        int dst[kLoads];
+#pragma unroll
+        for (int h = 0; h < kLoads; h++) {
+            const bool ok = n < nn;
+            dst[h] = ok ? n * blk + o : -1;
+            v[h] = ok ? __builtin_nontemporal_load(P.Kbar + (srows[2 * n] + o)) : 0.0;
+            n += dn;
+            o += dof;
+            if (o >= bsz) {
+                o -= bsz;
+                n++;
+            }
+        }
+        if (x0 == 0) {
+            // tables while the first values are on their way
+            for (int x = tid; x < NEN * NEN * D2; x += kThreads) {
+                if (PREC == kF64) sM[x] = (T)A.M[x];
+                else sM[x] = (T)A.M32[x];
+            }
+            for (int p = tid; p < deg; p += kThreads) {
+                const int c1 = A.sig_pos_ptr[posoff + p + 1];
+                for (int c = A.sig_pos_ptr[posoff + p]; c < c1; c++) {
+                    const int code = A.sig_contrib[c];
+                    const int k = code >> 16, i = (code >> 8) & 255, j = code & 255;
+                    tab[k * NEN + j] = (uint16_t)p;
+                    if (i == j) loc[k] = (uint8_t)i;
+                }
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < kLoads; h++)
+            if (dst[h] >= 0) stage[dst[h]] = v[h];
+    }
+    __syncthreads();
+    if (diag)
+        backward_items<DIM, NEN, PREC, MASK, kMayDiag>(P, nn, deg, blk, K, rkoff, eoff, stage, sM, tab, loc,
+                                                       n2l, w, lane, fe, G);
+    else
+        backward_items<DIM, NEN, PREC, MASK, false>(P, nn, deg, blk, K, rkoff, eoff, stage, sM, tab, loc,
+                                                    n2l, w, lane, fe, G);
+}
+
+// fixed[x]: bit DIM i + a where dof a of node i of plan column x's element is fixed
+template <int DIM, int NEN>
+__global__ __launch_bounds__(256) void k_backward_fixed(BwdGroupParams P) {
+    static_assert(DIM * NEN <= 32, "one word per element");
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (x >= P.A.n_cells) return;
+    const int64_t e = P.A.elem_by_rank ? P.A.elem_by_rank[x] : x;
+    uint32_t b = 0;
+#pragma unroll
+    for (int i = 0; i < NEN; i++) {
+        const int64_t n = P.cells[e * NEN + i];
+#pragma unroll
+        for (int a = 0; a < DIM; a++) b |= P.mask[DIM * n + a] ? 1u << (DIM * i + a) : 0u;
+    }
+    P.fixed[x] = b;
+}
+
+// drho_e = E'(rho_e) |det J| sum_i part(e, i), plan column by plan column
+template <int DIM, int NEN, int PREC>
+__global__ __launch_bounds__(256) void k_backward_sum(BwdGroupParams P) {
+    const AsmParams &A = P.A;
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x, NC = A.n_cells;
+    if (x >= NC) return;
+    const int64_t e = A.elem_by_rank ? A.elem_by_rank[x] : x;
+    double v[NEN];
+#pragma unroll
+    for (int i = 0; i < NEN; i++) v[i] = P.part[(int64_t)i * NC + x];
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < NEN; i++) s += v[i];
+    const double r = load_rho<PREC>(A.rho, e);
+    const double dE = A.p * simp_pow(r, A.p - 1.0, A.ip >= 1 ? A.ip - 1 : -1) * (A.E0 - A.Emin);
+    store_out<PREC>(P.drho, e, dE * A.geo[(int64_t)DIM * DIM * NC + x] * s);
+}
+
 // ---------------------------------------------------------------- launchers
+
+// Lets a kernel use `lds` bytes of dynamic LDS on the current device and says
+// how many of its workgroups a CU then holds (both kept per device).
+static hipError_t resident_blocks(const void *fn, int threads, size_t lds, int *per_cu) {
+    static std::mutex mu;
+    static std::map<std::pair<int, const void *>, size_t> lds_limit;
+    static std::map<std::tuple<int, const void *, size_t>, int> occupancy;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(mu);
+    size_t &lim = lds_limit[{dev, fn}];
+    if (lds > lim) {
+        e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        lim = lds;
+    }
+    auto it = occupancy.find({dev, fn, lds});
+    if (it == occupancy.end()) {
+        int n = 0;
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds);
+        if (e != hipSuccess || n < 1) n = 1;
+        it = occupancy.emplace(std::make_tuple(dev, fn, lds), n).first;
+    }
+    *per_cu = it->second;
+    return hipSuccess;
+}
 
 template <int DIM, int NEN, int PREC, bool FUSE>
 static hipError_t launch_assemble_t(const AsmParams &P, int64_t ngroups, hipStream_t st) {
@@ -2299,6 +2586,54 @@ hipError_t launch_backward(int elem, int prec, const BwdParams &P, hipStream_t s
         return hipErrorInvalidValue;
     }
 #undef SOPTX_BW
+}
+
+template <int DIM, int NEN, int PREC>
+static hipError_t launch_backward_group_t(const BwdGroupParams &P0, int64_t ngroups, hipStream_t st) {
+    if (ngroups <= 0 || P0.A.n_cells <= 0) return hipSuccess;
+    const AsmParams &A = P0.A;
+    const size_t csz = PREC == kF64 ? 8 : 4;
+    const bool mask = P0.mask != nullptr;
+    const size_t lds = 8 * (size_t)A.stage + csz * NEN * NEN * DIM * DIM + kGroupNodes * 2 * 4 +
+                       2 * (size_t)A.kmax * NEN + (size_t)A.kmax;
+    if (lds + 64 > 160 * 1024) return hipErrorInvalidValue;
+    const void *fn = mask ? reinterpret_cast<const void *>(&k_backward_group<DIM, NEN, PREC, true>)
+                          : reinterpret_cast<const void *>(&k_backward_group<DIM, NEN, PREC, false>);
+    int per_cu = 0;
+    hipError_t e = resident_blocks(fn, OsShape<DIM>::threads, lds, &per_cu);
+    if (e != hipSuccess) return e;
+    BwdGroupParams P = P0;
+    const int ncu = A.n_cu > 0 ? A.n_cu : 256;
+    P.A.os_window = std::max(8, (per_cu * ncu) / 8 * 8);
+    const dim3 g((unsigned)ngroups), b(OsShape<DIM>::threads);
+    const dim3 ge((unsigned)((A.n_cells + 255) / 256));
+    if (mask) {
+        hipLaunchKernelGGL((k_backward_fixed<DIM, NEN>), ge, dim3(256), 0, st, P);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_backward_group<DIM, NEN, PREC, true>), g, b, lds, st, P);
+    }
+    else hipLaunchKernelGGL((k_backward_group<DIM, NEN, PREC, false>), g, b, lds, st, P);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_backward_sum<DIM, NEN, PREC>), ge, dim3(256), 0, st, P);
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_group(int elem, int prec, const BwdGroupParams &P, int64_t ngroups, hipStream_t st) {
+#define SOPTX_BG(E, D, N)                                                              \
+    case E:                                                                            \
+        if (prec == kF64) return launch_backward_group_t<D, N, kF64>(P, ngroups, st);  \
+        return launch_backward_group_t<D, N, kF32>(P, ngroups, st);
+    switch (elem) {
+        SOPTX_BG(SOPTX_QUAD4, 2, 4)
+        SOPTX_BG(SOPTX_TRI3, 2, 3)
+        SOPTX_BG(SOPTX_HEX8, 3, 8)
+        SOPTX_BG(SOPTX_TET10, 3, 10)
+    default:
+        return hipErrorInvalidValue;
+    }
+#undef SOPTX_BG
 }
 
 // ------------------------------------------------ allocation-free evaluate

@@ -58,6 +58,26 @@ int get_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
     return SOPTX_OK;
 }
 
+bool have_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
+    {
+        std::lock_guard<std::mutex> lk(g_ws_mu);
+        auto it = g_ws.find(std::make_tuple(device, st, use));
+        if (it != g_ws.end() && it->second.n >= n) {
+            *out = it->second.buf;
+            return true;
+        }
+    }
+    // memory cannot be allocated while the stream is being captured
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (get_workspace(device, st, n, out, use) == SOPTX_OK) return true;
+    (void)hipGetLastError();
+    return false;
+}
+
 }  // namespace soptx
 
 
@@ -681,12 +701,26 @@ int soptx_assemble_backward(soptx_pattern h, const soptx_material *m, const void
     if (h->n_cells == 0) return SOPTX_OK;
     DeviceGuard dg(h->device);
     if (!dg.ok) return SOPTX_E_DEVICE;
+    // On the plan's node groups, with the parts of each element in the
+    // stream's workspace; the element-by-element kernel where that memory
+    // cannot be had (a first call while the stream is being captured, or a
+    // full device): it needs no workspace.
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    double *part = nullptr;
+    if (have_workspace(h->device, st, (size_t)h->n_cells * (h->nen + 1), &part, 5)) {
+        BwdGroupParams B{};
+        if ((rc = asm_params(h, m, d_rho, nullptr, prec, st, B.A))) return rc;
+        B.Kbar = d_Kbar; B.mask = d_dirichlet; B.cells = h->cells; B.part = part;
+        B.fixed = reinterpret_cast<uint32_t *>(part + h->n_cells * h->nen); B.drho = d_drho;
+        if (launch_backward_group(h->elem, prec, B, h->ngroups, st) != hipSuccess) return SOPTX_E_DEVICE;
+        return SOPTX_OK;
+    }
     BwdParams P{};
     P.cells = h->cells; P.row_ptr = h->row_ptr; P.pos = h->pos; P.geo = h->geo; P.rho = d_rho;
     P.Kbar = d_Kbar; P.M = h->M; P.M32 = h->M32; P.drho = d_drho; P.mask = d_dirichlet;
     P.n_cells = h->n_cells; P.E0 = m->E0; P.Emin = m->Emin; P.p = m->p; P.ip = int_exponent(m->p);
     lame(h, m, &P.lam, &P.mu);
-    if (launch_backward(h->elem, prec, P, static_cast<hipStream_t>(stream)) != hipSuccess) return SOPTX_E_DEVICE;
+    if (launch_backward(h->elem, prec, P, st) != hipSuccess) return SOPTX_E_DEVICE;
     return SOPTX_OK;
 }
 
