@@ -704,10 +704,17 @@ int soptx_assemble_backward(soptx_pattern h, const soptx_material *m, const void
     // On the plan's node groups, with the parts of each element in the
     // stream's workspace; the element-by-element kernel where that memory
     // cannot be had (a first call while the stream is being captured, or a
-    // full device): it needs no workspace.
+    // full device): it needs no workspace.  It also serves small 2D meshes,
+    // whose calls cost their launches (two or three against one): without and
+    // with a mask, 10,000 quadrilaterals 8.8 and 14.9 us against 11.8 and
+    // 14.9, 20,000 triangles 8.8 and 9.5 against 12.0 and 14.7; 25,000
+    // renumbered quadrilaterals 16.6 and 34.2 against 11.9 and 14.9, 100,000
+    // triangles 11.0 and 15.7 against 13.1 and 15.9 (in 3D 2,000 hexahedra
+    // 101 against 14).
     hipStream_t st = static_cast<hipStream_t>(stream);
     double *part = nullptr;
-    if (have_workspace(h->device, st, (size_t)h->n_cells * (h->nen + 1), &part, 5)) {
+    const bool small = h->dim == 2 && h->n_cells <= 20000;
+    if (!small && have_workspace(h->device, st, (size_t)h->n_cells * (h->nen + 1), &part, 5)) {
         BwdGroupParams B{};
         if ((rc = asm_params(h, m, d_rho, nullptr, prec, st, B.A))) return rc;
         B.Kbar = d_Kbar; B.mask = d_dirichlet; B.cells = h->cells; B.part = part;

@@ -23,8 +23,10 @@ pytestmark = pytest.mark.gpu
 MAT = api.Material()
 
 # (element, mesh sizes): one cell; a few groups with remainders; nodes of full
-# groups on every side
-SIZES = [(I.QUAD4, (1, 1)), (I.QUAD4, (35, 33)), (I.TRI3, (1, 1)), (I.TRI3, (37, 34)), (I.HEX8, (1, 1, 1)),
+# groups on every side; 2D meshes on either side of 20,000 cells, up to which
+# the element-by-element kernel runs
+SIZES = [(I.QUAD4, (1, 1)), (I.QUAD4, (35, 33)), (I.QUAD4, (201, 100)), (I.TRI3, (1, 1)), (I.TRI3, (100, 100)),
+         (I.TRI3, (97, 107)), (I.HEX8, (1, 1, 1)),
          (I.HEX8, (2, 2, 35)), (I.HEX8, (7, 5, 9)), (I.TET10, (1, 1, 1)), (I.TET10, (3, 4, 5))]
 
 
