@@ -15,9 +15,11 @@
  * taken through the density filter's chain rule, vol equals the volume of the
  * filtered density exactly (the filter is linear in rho).
  *
- * The kernels take the same decisions as the sequential loop: each pass
- * evaluates the 15 midpoints the next 4 steps can visit (computed as the loop
- * computes them) and one block walks them.  vol is summed in a fixed order.
+ * The kernels take the same decisions as the sequential loop.  For eta 0.5 and
+ * 1 and tol >= 1e-5 the path is predicted and then proved from vol at its ends
+ * (vol is monotone in lambda there); otherwise, and where the proof fails, each
+ * pass evaluates the 15 midpoints the next 4 steps can reach and one block
+ * walks them.  vol is summed in a fixed order.
  *
  * Status codes are the SOPTX_* codes of soptx.h.
  */

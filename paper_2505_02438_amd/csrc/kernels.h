@@ -225,7 +225,22 @@ constexpr int kOcDepth = 4;
 constexpr int kOcNodes = (1 << kOcDepth) - 1;
 constexpr int kOcMaxBlocks = 1024;
 int oc_blocks(int64_t n);
-hipError_t launch_oc_init(double *st, double lmax, hipStream_t s);
+// multipliers per search launch, search launches, values that prove a path
+constexpr int kOcPoints = 63;
+constexpr int kOcSearch = 3;
+constexpr int kOcProof = 3;
+// the search sums: [search][copy][64] doubles; slots of the largest change
+constexpr int kOcCopies = 16;
+constexpr int kOcAcc = kOcSearch * kOcCopies * 64;
+constexpr int kOcSlots = 32;
+static_assert(kOcProof <= kOcNodes, "the proof's partials fit the passes' buffer");
+hipError_t launch_oc_init(double *st, double lmax, double *acc, hipStream_t s);
+// the bisection by search and proof: st[5] = 1, rho_new and the change (the
+// largest of st[8 .. 8 + kOcSlots), as bits) written if the path is proved, else
+// only st touched (launch_oc_init again before any pass)
+hipError_t launch_oc_direct(const double *rho, const double *dc, const double *dv, int64_t n, double move, double eta,
+                            double vol_target, double lmax, double tol, int max_steps, double *st, double *acc,
+                            double *part, double *out, hipStream_t s);
 hipError_t launch_oc_pass(const double *rho, const double *dc, const double *dv, int64_t n, double move, double eta,
                           double vol_target, double tol, int max_steps, double *st, double *part, hipStream_t s);
 hipError_t launch_oc_apply(const double *rho, const double *dc, const double *dv, int64_t n, double move, double eta,
