@@ -131,11 +131,26 @@ hipError_t launch_block_inv(int dim, const int32_t *row_ptr, const int32_t *nb, 
 hipError_t launch_cg_vec(int dim, int mode, const double *f, double *u, double *r, double *z, double *p,
                          const double *q, const double *binv, const double *sc, double *part, int64_t ndof,
                          hipStream_t st);
-hipError_t launch_cg_vec_fused(int dim, double *u, double *r, double *z, double *p, const double *q,
-                               const double *binv, const double *pq_part, int n_pq, const double *sc,
-                               double *part_out, int64_t ndof, hipStream_t st);
-hipError_t launch_cg_p_fused(double *p, const double *z, const double *part, int nb, const double *sc_cur,
-                             double *sc_next, int64_t n, hipStream_t st);
+// the two-launch iteration of small systems (k_cg_step_spmv, k_cg_step_vec)
+struct CgStep {
+    const int32_t *row_ptr, *nb;
+    const double *K, *binv;
+    double *u, *r, *z, *q;
+    double *p[2];      // iteration `it` writes p[it & 1]
+    double *pq_part;   // [n_pq]
+    double *rz_part;   // [2][n_rz]: r.z, r.r
+    int n_pq, n_rz;
+    double *sc;        // r.z of iteration it in sc[8 (it & 1)]
+    double *fin;       // [0] stopped, [1] iterations, [2] r.r; host: the same in host memory
+    double *host;
+    double ref, rtol;  // stop where sqrt(r.r / ref) <= rtol
+    int64_t n_nodes;
+};
+// iteration `it`'s first launch; check: the residual of the `it` iterations so far
+hipError_t launch_cg_step(int dim, const CgStep &A, int it, bool check, hipStream_t st);
+hipError_t launch_cg_step_vec(int dim, const CgStep &A, int it, hipStream_t st);
+hipError_t launch_cg_clear(double *x, int n, hipStream_t st);  // n <= 64 doubles to 0
+hipError_t launch_cg_step_end(const CgStep &A, int it, hipStream_t st);
 hipError_t launch_cg_p(double *p, const double *z, const double *sc, int64_t n, hipStream_t st);
 hipError_t launch_cg_scalars(int what, const double *part, int n, double *sc, hipStream_t st);
 hipError_t launch_backward(int elem, int prec, const BwdParams &P, hipStream_t st);

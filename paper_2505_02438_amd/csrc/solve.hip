@@ -202,66 +202,287 @@ __global__ __launch_bounds__(256) void k_cg_p(double *__restrict__ p, const doub
     if (i < n) p[i] = z[i] + sc[2] * p[i];
 }
 
-// The sum of n block partials in the order of k_cg_scalars (1024 strided
-// sums, then a halving tree), computed by one block of 256 threads: thread t
-// holds the strided sums t, t + 256, t + 512 and t + 768, does the tree's
-// first two levels itself and block_sum_256 the rest.  Every block that calls
-// it gets the same bits.
-__device__ __forceinline__ double sum_as_scalars(const double *__restrict__ part, int n, double *red) {
-    double v[4] = {0.0, 0.0, 0.0, 0.0};
+// ---- The iteration of small systems: two launches.
+//
+// k_cg_step_spmv forms beta and p = z + beta p (at every gathered node, the
+// node's own into the other of two p buffers) and q = K p with the partials of
+// p.q; k_cg_step_vec forms alpha, then u, r, z and the partials of r.z and r.r.
+// Every block adds the partials of the launch before it, in the order of
+// k_cg_scalars, so that no launch is needed for the two scalars; the sums and
+// every product are those of the separate kernels above, bit for bit.  At
+// these sizes an iteration is launches and chains of loads: K is read from
+// the last-level cache.  So what the scalar does not touch (K, the neighbours'
+// z and p, the node's own vectors) is read ahead of the partials.
+// 120x40x8 hexahedra (133,947 dofs), per iteration: 18.5 + 5.5 us, 24.2 in all,
+// against three launches of 16.2, 8.1 and 4.7 us and a host read every 8
+// iterations (32.3); the 150x50 quadrilaterals 4.3 + 3.0 us, 8.2 in all, against
+// 3.7, 4.8 and 3.6 us (18.3; there the host's 3.7 us per launch are the floor).
+// In the first launch K is 75 MB of loads, each line touched by two of them:
+// with non-temporal loads (no reuse in the first cache) it takes 28 us; K
+// through LDS in whole lines 25, z and p side by side 19.6, one neighbour ahead
+// instead of two 20.7, a contiguous eighth of the nodes per XCD 19.2, every wave
+// adding the partials itself (no barrier) 22.
+//
+// The residual is checked on the device every kCgCheck iterations, by block 0
+// of the launch that starts the next one; launches after a stop return at
+// once, so the host can enqueue ahead instead of waiting for each check.  fin:
+// [0] stopped, [1] iterations, [2] r.r.
+
+// x + its DPP partner
+template <int CTRL>
+__device__ __forceinline__ double add_dpp(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
+    return x + __hiloint2double(hi, lo);
+}
+
+// N sums over a block of 256 threads, each in block_sum_256's order, returned
+// to every thread, with one barrier (two where red is reused: `again`): every
+// wave adds the 256 values itself, lane l the sixteen l + 16 j (the tree's
+// first four levels), then the rest within a row of 16 lanes.
+template <int N>
+__device__ __forceinline__ void block_sums_256(double (&x)[N], double (*red)[256], bool again) {
+    if (again) __syncthreads();
 #pragma unroll
-    for (int g = 0; g < 4; g++)
-        for (int k = (int)threadIdx.x + 256 * g; k < n; k += 1024) v[g] += part[k];
+    for (int k = 0; k < N; k++) red[k][threadIdx.x] = x[k];
+    __syncthreads();
+    const int l = threadIdx.x & 15;
+#pragma unroll
+    for (int k = 0; k < N; k++) {
+        double v[16];
+#pragma unroll
+        for (int j = 0; j < 16; j++) v[j] = red[k][l + 16 * j];
+#pragma unroll
+        for (int st = 8; st > 0; st >>= 1)
+#pragma unroll
+            for (int j = 0; j < st; j++) v[j] += v[j + st];
+        double t = add_dpp<0x108>(v[0]);  // row_shl: lane l + 8, 4, 2, 1
+        t = add_dpp<0x104>(t);
+        t = add_dpp<0x102>(t);
+        t = add_dpp<0x101>(t);
+        x[k] = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(t)),
+                                __builtin_amdgcn_readfirstlane(__double2loint(t)));
+    }
+}
+
+// Thread t's share of the sum of n block partials in the order of k_cg_scalars
+// (1024 strided sums, then a halving tree): the strided sums t, t + 256, t +
+// 512 and t + 768 and the tree's first two levels; block_sums_256 does the
+// rest.
+template <int ROUNDS>
+__device__ __forceinline__ double scalar_share(const double *__restrict__ part, int n) {
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    // ROUNDS rounds of loads in flight together, then added in order
+    for (int k0 = threadIdx.x; k0 < n; k0 += ROUNDS * 1024) {
+        double x[ROUNDS][4];
+#pragma unroll
+        for (int h = 0; h < ROUNDS; h++)
+#pragma unroll
+            for (int g = 0; g < 4; g++) {
+                const int k = k0 + 256 * g + 1024 * h;
+                x[h][g] = k < n ? part[k] : 0.0;
+            }
+#pragma unroll
+        for (int h = 0; h < ROUNDS; h++)
+#pragma unroll
+            for (int g = 0; g < 4; g++)
+                if (k0 + 256 * g + 1024 * h < n) v[g] += x[h][g];
+    }
     v[0] += v[2];
     v[1] += v[3];
-    v[0] += v[1];
-    return block_sum_256(v[0], red);
+    return v[0] + v[1];
 }
 
-// Fused iteration step for small systems: every block first forms
-// alpha = r.z / p.q from the SpMV's partials (as k_cg_scalars would), then
-// does k_cg_vec's mode 1.  Scalars are double-buffered by iteration parity
-// (slot sc + 8 par holds this iteration's r.z); partials of r.z, r.r go to
-// part_out, a different array from the p.q partials every block is reading.
-template <int DIM>
-__global__ __launch_bounds__(256) void k_cg_vec_fused(double *__restrict__ u, double *__restrict__ r,
-                                                      double *__restrict__ z, double *__restrict__ p,
-                                                      const double *__restrict__ q, const double *__restrict__ binv,
-                                                      const double *__restrict__ pq_part, int n_pq,
-                                                      const double *__restrict__ sc, double *__restrict__ part_out,
-                                                      int64_t n_nodes) {
-    __shared__ double red[256];
-    const double al = sc[0] / sum_as_scalars(pq_part, n_pq, red);
-    const int64_t I = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double rz = 0.0, rr = 0.0;
-    if (I < n_nodes) cg_node<DIM>(1, al, I, nullptr, u, r, z, p, q, binv, rz, rr);
-    const double brz = block_sum_256(rz, red);
-    const double brr = block_sum_256(rr, red);
-    if (threadIdx.x == 0) {
-        part_out[blockIdx.x] = brz;
-        part_out[gridDim.x + blockIdx.x] = brr;
+// sum over the L lanes of a node by the xor tree of k_spmv
+template <int L>
+__device__ __forceinline__ double lanes_sum(double x) {
+    static_assert(L == 16 || L == 8, "rows of 16 or 8 lanes");
+    if (L == 16) {
+        // a rotation by half the period is the xor partner
+        x = add_dpp<0x128>(x);
+        x = add_dpp<0x124>(x);
+        x = add_dpp<0x122>(x);
+        return add_dpp<0x121>(x);
     }
+    // xor 4: mirror within 8 lanes (xor 7), then reverse each quad (xor 3)
+    int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x141, 0xf, 0xf, true);
+    int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x141, 0xf, 0xf, true);
+    lo = __builtin_amdgcn_update_dpp(0, lo, 0x1b, 0xf, 0xf, true);
+    hi = __builtin_amdgcn_update_dpp(0, hi, 0x1b, 0xf, 0xf, true);
+    x += __hiloint2double(hi, lo);
+    x = add_dpp<0x4e>(x);     // quad lanes 2 3 0 1: xor 2
+    return add_dpp<0xb1>(x);  // quad lanes 1 0 3 2: xor 1
 }
 
-// Fused p step: every block forms beta = new r.z / r.z from the partials and
-// updates p; block 0 writes the next iteration's scalars (new r.z, r.r) into
-// the other parity slot, which no block of this launch reads.
-__global__ __launch_bounds__(256) void k_cg_p_fused(double *__restrict__ p, const double *__restrict__ z,
-                                                    const double *__restrict__ part, int nb, const double *sc_cur,
-                                                    double *sc_next, int64_t n) {
-    __shared__ double red[256];
-    const double rz = sum_as_scalars(part, nb, red);
-    const double beta = rz / sc_cur[0];
-    if (blockIdx.x == 0) {
-        const double rr = sum_as_scalars(part + nb, nb, red);
-        if (threadIdx.x == 0) {
-            sc_next[0] = rz;
-            sc_next[2] = beta;
-            sc_next[3] = rr;
+template <int DIM, int L>
+__global__ __launch_bounds__(256) void k_cg_step_spmv(CgStep A, int it, bool check) {
+    __shared__ double red[1][256];
+    const bool stopped = A.fin[0] != 0.0;  // looked at before the first write: nothing waits for it alone
+    const bool first = it == 0;            // p = z
+    const double *__restrict__ z = A.z;
+    const double *__restrict__ po = A.p[(it & 1) ^ 1];
+    double *__restrict__ pn = A.p[it & 1];
+    const int sub = threadIdx.x % L;
+    const int64_t I = ((int64_t)blockIdx.x * 256 + threadIdx.x) / L;
+    const bool live = I < A.n_nodes;
+    const double old = first ? 1.0 : A.sc[8 * ((it & 1) ^ 1)];
+    const double share = first ? 0.0 : scalar_share<1>(A.rz_part, A.n_rz);
+    // the lane's first kAhead neighbours and the node's own z and p
+    constexpr int kAhead = 2;
+    int b = 0, rl = 0, deg = 0, nbo = 0, J[kAhead];
+    double Kv[kAhead][DIM][DIM], zj[kAhead][DIM], pj[kAhead][DIM], zi[DIM], pi[DIM];
+    if (live) {
+        b = A.row_ptr[DIM * I];
+        rl = A.row_ptr[DIM * I + 1] - b;
+        deg = rl / DIM;
+        nbo = b / (DIM * DIM);
+    }
+#pragma unroll
+    for (int h = 0; h < kAhead; h++) J[h] = sub + h * L < deg ? A.nb[nbo + sub + h * L] : -1;
+#pragma unroll
+    for (int h = 0; h < kAhead; h++)
+        if (J[h] >= 0) {
+#pragma unroll
+            for (int a = 0; a < DIM; a++)
+#pragma unroll
+                for (int e = 0; e < DIM; e++) Kv[h][a][e] = A.K[b + a * rl + DIM * (sub + h * L) + e];
+#pragma unroll
+            for (int e = 0; e < DIM; e++) {
+                zj[h][e] = z[(int64_t)DIM * J[h] + e];
+                pj[h][e] = first ? 0.0 : po[(int64_t)DIM * J[h] + e];
+            }
+        }
+    if (live && sub == 0)
+#pragma unroll
+        for (int a = 0; a < DIM; a++) {
+            zi[a] = z[DIM * I + a];
+            pi[a] = first ? 0.0 : po[DIM * I + a];
+        }
+    double beta = 0.0;
+    if (!first) {
+        double t[1] = {share};
+        block_sums_256(t, red, false);
+        beta = t[0] / old;
+        if (blockIdx.x == 0 && !stopped) {
+            if (threadIdx.x == 0) A.sc[8 * (it & 1)] = t[0];
+            if (check) {
+                double s[1] = {scalar_share<1>(A.rz_part + A.n_rz, A.n_rz)};
+                block_sums_256(s, red, true);
+                // stop: converged, or broke down (NaN)
+                if (threadIdx.x == 0 && !(sqrt(s[0] / A.ref) > A.rtol)) {
+                    A.fin[1] = A.host[1] = (double)it;
+                    A.fin[2] = A.host[2] = s[0];
+                    A.fin[0] = A.host[0] = 1.0;
+                }
+            }
         }
     }
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        p[i] = z[i] + beta * p[i];
+    double acc[DIM];
+#pragma unroll
+    for (int a = 0; a < DIM; a++) acc[a] = 0.0;
+#pragma unroll
+    for (int h = 0; h < kAhead; h++)
+        if (J[h] >= 0) {
+            double x[DIM];
+#pragma unroll
+            for (int e = 0; e < DIM; e++) x[e] = first ? zj[h][e] : fma(beta, pj[h][e], zj[h][e]);
+#pragma unroll
+            for (int a = 0; a < DIM; a++)
+#pragma unroll
+                for (int e = 0; e < DIM; e++) acc[a] = fma(Kv[h][a][e], x[e], acc[a]);
+        }
+    for (int q = sub + kAhead * L; q < deg; q += L) {
+        const int64_t d0 = (int64_t)DIM * A.nb[nbo + q];
+        double x[DIM];
+#pragma unroll
+        for (int e = 0; e < DIM; e++) x[e] = first ? z[d0 + e] : fma(beta, po[d0 + e], z[d0 + e]);
+#pragma unroll
+        for (int a = 0; a < DIM; a++)
+#pragma unroll
+            for (int e = 0; e < DIM; e++) acc[a] = fma(A.K[b + a * rl + DIM * q + e], x[e], acc[a]);
+    }
+#pragma unroll
+    for (int a = 0; a < DIM; a++) acc[a] = lanes_sum<L>(acc[a]);
+    if (stopped) return;
+    double xy[1] = {0.0};
+    if (live && sub == 0) {
+#pragma unroll
+        for (int a = 0; a < DIM; a++) {
+            const double x = first ? zi[a] : fma(beta, pi[a], zi[a]);
+            pn[DIM * I + a] = x;
+            A.q[DIM * I + a] = acc[a];
+            xy[0] = fma(x, acc[a], xy[0]);
+        }
+    }
+    block_sums_256(xy, red, !first);
+    if (threadIdx.x == 0) A.pq_part[blockIdx.x] = xy[0];
+}
+
+template <int DIM>
+__global__ __launch_bounds__(256) void k_cg_step_vec(CgStep A, int it) {
+    __shared__ double red[2][256];
+    const bool stopped = A.fin[0] != 0.0;
+    const int64_t I = (int64_t)blockIdx.x * 256 + threadIdx.x, d0 = DIM * I;
+    const bool live = I < A.n_nodes;
+    const double *__restrict__ p = A.p[it & 1];
+    double uu[DIM], rr[DIM], pp[DIM], qq[DIM], bi[DIM * DIM];
+    if (live) {
+#pragma unroll
+        for (int a = 0; a < DIM; a++) {
+            uu[a] = A.u[d0 + a];
+            rr[a] = A.r[d0 + a];
+            pp[a] = p[d0 + a];
+            qq[a] = A.q[d0 + a];
+        }
+#pragma unroll
+        for (int c = 0; c < DIM * DIM; c++) bi[c] = A.binv[DIM * DIM * I + c];
+    }
+    const double rz = A.sc[8 * (it & 1)];
+    double t[1] = {scalar_share<4>(A.pq_part, A.n_pq)};
+    block_sums_256(t, red, false);
+    if (stopped) return;
+    const double al = rz / t[0];
+    double s[2] = {0.0, 0.0};  // r.z, r.r
+    if (live) {
+        double ri[DIM];
+#pragma unroll
+        for (int a = 0; a < DIM; a++) {
+            A.u[d0 + a] = fma(al, pp[a], uu[a]);
+            ri[a] = fma(-al, qq[a], rr[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < DIM; a++) {
+            double v = 0.0;
+#pragma unroll
+            for (int c = 0; c < DIM; c++) v = fma(bi[a * DIM + c], ri[c], v);
+            A.r[d0 + a] = ri[a];
+            A.z[d0 + a] = v;
+            s[0] = fma(ri[a], v, s[0]);
+            s[1] = fma(ri[a], ri[a], s[1]);
+        }
+    }
+    block_sums_256(s, red, true);
+    if (threadIdx.x == 0) {
+        A.rz_part[blockIdx.x] = s[0];
+        A.rz_part[A.n_rz + blockIdx.x] = s[1];
+    }
+}
+
+__global__ void k_cg_clear(double *x, int n) {
+    if ((int)threadIdx.x < n) x[threadIdx.x] = 0.0;
+}
+
+// r.r after the last iteration, where no check stopped earlier
+__global__ __launch_bounds__(256) void k_cg_step_end(CgStep A, int it) {
+    __shared__ double red[1][256];
+    if (A.fin[0] != 0.0) return;
+    double s[1] = {scalar_share<1>(A.rz_part + A.n_rz, A.n_rz)};
+    block_sums_256(s, red, false);
+    if (threadIdx.x == 0) {
+        A.host[1] = (double)it;
+        A.host[2] = s[0];
+        A.host[0] = 1.0;
+    }
 }
 
 // One block of kScalThreads: sums of n block partials, thread t taking
@@ -349,26 +570,28 @@ hipError_t launch_cg_vec(int dim, int mode, const double *f, double *u, double *
     return hipGetLastError();
 }
 
-hipError_t launch_cg_vec_fused(int dim, double *u, double *r, double *z, double *p, const double *q,
-                               const double *binv, const double *pq_part, int n_pq, const double *sc,
-                               double *part_out, int64_t ndof, hipStream_t st) {
-    const unsigned g = (unsigned)cg_vec_blocks(dim, ndof);
-    if (g == 0) return hipSuccess;
-    if (dim == 3)
-        hipLaunchKernelGGL(k_cg_vec_fused<3>, dim3(g), dim3(256), 0, st, u, r, z, p, q, binv, pq_part, n_pq, sc,
-                           part_out, ndof / 3);
-    else
-        hipLaunchKernelGGL(k_cg_vec_fused<2>, dim3(g), dim3(256), 0, st, u, r, z, p, q, binv, pq_part, n_pq, sc,
-                           part_out, ndof / 2);
+hipError_t launch_cg_step(int dim, const CgStep &A, int it, bool check, hipStream_t st) {
+    const unsigned g = (unsigned)spmv_blocks(dim, A.n_nodes);
+    if (g == 0) return hipErrorInvalidValue;
+    if (dim == 3) hipLaunchKernelGGL((k_cg_step_spmv<3, 16>), dim3(g), dim3(256), 0, st, A, it, check);
+    else hipLaunchKernelGGL((k_cg_step_spmv<2, 8>), dim3(g), dim3(256), 0, st, A, it, check);
     return hipGetLastError();
 }
 
-hipError_t launch_cg_p_fused(double *p, const double *z, const double *part, int nb, const double *sc_cur,
-                             double *sc_next, int64_t n, hipStream_t st) {
-    const int64_t g0 = (n + 255) / 256;
-    const unsigned g = (unsigned)(g0 < 1024 ? g0 : 1024);
-    if (g == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cg_p_fused, dim3(g), dim3(256), 0, st, p, z, part, nb, sc_cur, sc_next, n);
+hipError_t launch_cg_step_vec(int dim, const CgStep &A, int it, hipStream_t st) {
+    const unsigned g = (unsigned)A.n_rz;
+    if (dim == 3) hipLaunchKernelGGL(k_cg_step_vec<3>, dim3(g), dim3(256), 0, st, A, it);
+    else hipLaunchKernelGGL(k_cg_step_vec<2>, dim3(g), dim3(256), 0, st, A, it);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_clear(double *x, int n, hipStream_t st) {
+    hipLaunchKernelGGL(k_cg_clear, dim3(1), dim3(64), 0, st, x, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_cg_step_end(const CgStep &A, int it, hipStream_t st) {
+    hipLaunchKernelGGL(k_cg_step_end, dim3(1), dim3(256), 0, st, A, it);
     return hipGetLastError();
 }
 

@@ -81,6 +81,62 @@ bool have_workspace(int device, hipStream_t st, size_t n, double **out, int use)
 }  // namespace soptx
 
 
+namespace {
+// A record in host memory that kernels write (a stop of the CG), with an event;
+// a small pool per device, given back after each call.
+struct StopRecord {
+    double *host = nullptr, *dev = nullptr;
+    hipEvent_t event = nullptr;
+    int device;
+    hipStream_t stream;
+    StopRecord(int d, hipStream_t st) : device(d), stream(st) {
+        {
+            std::lock_guard<std::mutex> lk(mu());
+            auto &free = pool()[device];
+            if (!free.empty()) {
+                std::tie(host, dev, event) = free.back();
+                free.pop_back();
+            }
+        }
+        if (!host) {
+            void *p = nullptr, *q = nullptr;
+            if (hipHostMalloc(&p, 64, hipHostMallocMapped) != hipSuccess) return;
+            if (hipHostGetDevicePointer(&q, p, 0) != hipSuccess ||
+                hipEventCreateWithFlags(&event, hipEventDisableTiming) != hipSuccess) {
+                (void)hipHostFree(p);
+                return;
+            }
+            host = static_cast<double *>(p);
+            dev = static_cast<double *>(q);
+        }
+        host[0] = host[1] = host[2] = 0.0;
+    }
+    ~StopRecord() {
+        if (!host) return;
+        // kernels of a call that failed may still write the record: they end first
+        (void)hipStreamSynchronize(stream);
+        std::lock_guard<std::mutex> lk(mu());
+        auto &free = pool()[device];
+        if (free.size() < 16) {
+            free.emplace_back(host, dev, event);
+            return;
+        }
+        (void)hipEventDestroy(event);
+        (void)hipHostFree(host);
+    }
+    StopRecord(const StopRecord &) = delete;
+    StopRecord &operator=(const StopRecord &) = delete;
+
+private:
+    using Slot = std::tuple<double *, double *, hipEvent_t>;
+    static std::mutex &mu() { static std::mutex m; return m; }
+    static std::map<int, std::vector<Slot>> &pool() {
+        static std::map<int, std::vector<Slot>> *p = new std::map<int, std::vector<Slot>>();
+        return *p;
+    }
+};
+}  // namespace
+
 struct soptx_pattern_s {
     int elem = 0, dim = 0, nen = 0, ref_method = 0, device = 0, nq = 0;
     int64_t n_nodes = 0, n_cells = 0, ndof = 0, nnz = 0, ngroups = 0, nsig = 0;
@@ -513,22 +569,23 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
     const int64_t nbv = cg_vec_blocks(h->dim, n);            // blocks of the vector kernels
     const int64_t nbs = spmv_blocks(h->dim, h->n_nodes);      // blocks of the SpMV
     const int64_t npart = std::max<int64_t>(3 * nbv, nbs);
-    // Small systems fuse the scalar steps into the vector kernels: each of
-    // their blocks re-reads the SpMV's partials, which pays while that is a few
-    // MB (nbs * nbv doubles); the fused and separate steps give the same bits.
-    const bool fused = nbs * nbv <= (int64_t)1 << 22;
+    // Small systems run two launches per iteration that form the scalars
+    // themselves: each of their blocks re-reads the other launch's partials,
+    // which pays while that is a few MB (nbs * nbv doubles); both forms give the
+    // same bits.
+    const bool small = nbs * nbv <= (int64_t)1 << 22;
     // r, z, p, q, the node blocks of the preconditioner (DIM doubles per dof),
-    // partials, the fused path's second partials, 2 x 8 scalars (parity slots)
+    // partials, 2 x 8 scalars, a stop record; small systems: a second p
     double *ws = nullptr;
-    int rc = get_workspace(h->device, st, (4 + (size_t)h->dim) * (size_t)n + (size_t)npart + 2 * (size_t)nbv + 16,
+    int rc = get_workspace(h->device, st, (4 + (size_t)h->dim + (small ? 1 : 0)) * (size_t)n + (size_t)npart +
+                                               2 * (size_t)nbv + 20,
                            &ws, 1);
     if (rc) return rc;
     double *r = ws, *z = r + n, *p = z + n, *q = p + n, *binv = q + n, *part = binv + h->dim * n,
-           *part2 = part + npart, *sc = part2 + 2 * nbv;
-    int par = 0;  // fused path: the scalar slot sc + 8 par holds this iteration's r.z
+           *part2 = part + npart, *sc = part2 + 2 * nbv, *fin = sc + 16, *p2 = fin + 4;
     double hs[8];
     auto scalars = [&]() {
-        if (hipMemcpyAsync(hs, sc + 8 * par, sizeof(hs), hipMemcpyDeviceToHost, st) != hipSuccess) return false;
+        if (hipMemcpyAsync(hs, sc, sizeof(hs), hipMemcpyDeviceToHost, st) != hipSuccess) return false;
         return hipStreamSynchronize(st) == hipSuccess;
     };
     // r = f - K u, z = B^-1 r, p = z
@@ -550,25 +607,51 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
         *h_relres = std::sqrt(rr0 / ref);
         return SOPTX_OK;
     }
-    // the residual is read back every kCheck iterations
+    // the residual is checked every kCheck iterations
     constexpr int kCheck = 8;
     int it = 0;
     double rel = 1.0;
-    while (it < max_iter) {
-        if (launch_spmv(h->dim, h->row_ptr, h->nb, d_K_vals, p, q, part, h->n_nodes, st) != hipSuccess)
-            return SOPTX_E_DEVICE;
-        if (fused) {
-            if (launch_cg_vec_fused(h->dim, d_u, r, z, p, q, binv, part, (int)nbs, sc + 8 * par, part2, n, st) !=
-                    hipSuccess ||
-                launch_cg_p_fused(p, z, part2, (int)nbv, sc + 8 * par, sc + 8 * (1 - par), n, st) != hipSuccess)
-                return SOPTX_E_DEVICE;
-            par = 1 - par;
-        } else if (launch_cg_scalars(1, part, (int)nbs, sc, st) != hipSuccess ||
-                   launch_cg_vec(h->dim, 1, d_f, d_u, r, z, p, q, binv, sc, part, n, st) != hipSuccess ||
-                   launch_cg_scalars(2, part, (int)nbv, sc, st) != hipSuccess ||
-                   launch_cg_p(p, z, sc, n, st) != hipSuccess) {
-            return SOPTX_E_DEVICE;
+    if (small && max_iter > 0) {
+        StopRecord rec(h->device, st);
+        if (!rec.host) return SOPTX_E_OOM;
+        CgStep A{};
+        A.row_ptr = h->row_ptr; A.nb = h->nb; A.K = d_K_vals; A.binv = binv;
+        A.u = d_u; A.r = r; A.z = z; A.q = q; A.p[0] = p; A.p[1] = p2;
+        A.pq_part = part; A.rz_part = part2; A.n_pq = (int)nbs; A.n_rz = (int)nbv;
+        A.sc = sc; A.fin = fin; A.host = rec.dev; A.ref = ref; A.rtol = rtol; A.n_nodes = h->n_nodes;
+        // the record of a stop starts as "none"
+        if (launch_cg_clear(fin, 4, st) != hipSuccess) return SOPTX_E_DEVICE;
+        // The launches of kAhead iterations past a check are enqueued before
+        // its result is waited for, so the device does not idle meanwhile.
+        constexpr int kAhead = 4;
+        bool waiting = false;
+        for (it = 0; it < max_iter; it++) {
+            const bool check = it > 0 && it % kCheck == 0;
+            if (launch_cg_step(h->dim, A, it, check, st) != hipSuccess) return SOPTX_E_DEVICE;
+            if (check) {
+                if (hipEventRecord(rec.event, st) != hipSuccess) return SOPTX_E_DEVICE;
+                waiting = true;
+            }
+            if (launch_cg_step_vec(h->dim, A, it, st) != hipSuccess) return SOPTX_E_DEVICE;
+            if (waiting && it % kCheck == kAhead) {
+                waiting = false;
+                if (hipEventSynchronize(rec.event) != hipSuccess) return SOPTX_E_DEVICE;
+                if (rec.host[0] != 0.0) break;
+            }
         }
+        if (launch_cg_step_end(A, max_iter, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+            return SOPTX_E_DEVICE;
+        *h_iters = (int32_t)rec.host[1];
+        *h_relres = std::sqrt(rec.host[2] / ref);
+        return SOPTX_OK;
+    }
+    while (it < max_iter) {
+        if (launch_spmv(h->dim, h->row_ptr, h->nb, d_K_vals, p, q, part, h->n_nodes, st) != hipSuccess ||
+            launch_cg_scalars(1, part, (int)nbs, sc, st) != hipSuccess ||
+            launch_cg_vec(h->dim, 1, d_f, d_u, r, z, p, q, binv, sc, part, n, st) != hipSuccess ||
+            launch_cg_scalars(2, part, (int)nbv, sc, st) != hipSuccess ||
+            launch_cg_p(p, z, sc, n, st) != hipSuccess)
+            return SOPTX_E_DEVICE;
         it++;
         if (it % kCheck == 0 || it == max_iter) {
             if (!scalars()) return SOPTX_E_DEVICE;
