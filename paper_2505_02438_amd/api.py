@@ -70,7 +70,8 @@ def host_plan(elem: int, coords, cells, general: bool = False) -> dict:
         for name in ("row_ptr", "col_idx", "geo", "sig_info", "sig_pos_ptr", "sig_contrib", "sig_pairs", "sig_witems", "sig_witem_ptr",
                      "grp_info", "grp_nodes", "grp_elems", "grp_n2l", "grp_rows", "grp_rank_off", "grp_rank", "elem_by_rank", "pos", "nb_tslot",
                      "nb_tdeg",
-                     "gptr", "gent", "gnode", "qgeo"):
+                     "gptr", "gent", "gnode", "qgeo",
+                     "rg_info", "rg_rows", "rg_vis", "rg_pairs", "rg_code", "rg_ext"):
             ptr, cnt, eb = ctypes.c_void_p(), ctypes.c_int64(), ctypes.c_int32()
             check(L.soptx_debug_host_plan_array(h, name.encode(), ctypes.byref(ptr), ctypes.byref(cnt),
                                                 ctypes.byref(eb)), name)

@@ -24,6 +24,17 @@ constexpr int kGrpDiag = 1;  // every element of the group has a diagonal J^-1 (
 constexpr int kGrpWideShift = 1;
 constexpr int kWideInts = 32;  // ints per wide work item: P, Q, T, 0 x 5, p[8], off[8], cnt[8]
 
+// row groups of Q2 hexahedra: visits, pairs, rows and blocks of three or more
+// terms per group, and doubles of LDS for the row blocks and the slots of
+// third and later terms (four workgroups per CU)
+constexpr int kRgVisits = 8;
+constexpr int kRgPairs = 14;
+constexpr int kRgRows = 16;
+constexpr int kRgExt = 28;
+constexpr int kRgStage = 5056;
+constexpr int kRgSecond = 0x4000;
+constexpr int kRgSlot = 0x8000;
+
 inline int elem_dim(int elem) {
     switch (elem) {
     case SOPTX_QUAD4: case SOPTX_TRI3: return 2;
@@ -114,6 +125,19 @@ struct HostPlan {
     // canonical plan) and Gauss point q, sqrt(w_q |det J_q|) J_q^-1,
     // [NQ][dim][dim][n_cells]
     std::vector<double> qgeo;
+    // Q2 hexahedra: row groups of the fused assembly (k_assemble_hex27; empty
+    // where a node does not fit its limits).  A group is a set of nodes (rows),
+    // the elements around them (visits, ascending) and, per visit, its rows two
+    // at a time (pairs).  Local nodes by lattice index a + 3 b + 9 c.
+    std::vector<int32_t> rg_info;   // [groups][4]: rows, pairs, doubles of the row blocks, blocks of three or more terms
+    std::vector<int32_t> rg_rows;   // [groups][kRgRows][4]: first CSR slot, degree, first double in the stage, node
+    std::vector<int32_t> rg_vis;    // [groups][kRgVisits]: element (the first one again past the last)
+    std::vector<int32_t> rg_pairs;  // [groups][kRgPairs][2]: visit | i0 << 8 | i1 << 16 (i1 = 255: none), row0 | row1 << 16
+    std::vector<uint16_t> rg_code;  // [groups][kRgPairs][2][27]: the block's position in the row, | kRgSecond where an
+                                    // earlier visit of the group has its first term; or kRgSlot | slot for a third
+                                    // or later term
+    std::vector<int32_t> rg_ext;    // [groups][kRgExt][2], blocks of three or more terms: first double in the stage,
+                                    // then 3 deg | first slot << 12 | slots << 24
     int64_t n_groups() const { return (int64_t)grp_info.size() / kGrpInfo; }
     int64_t n_sigs() const { return (int64_t)sig_info.size() / 4; }
 };

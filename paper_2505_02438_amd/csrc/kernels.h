@@ -187,6 +187,22 @@ hipError_t launch_assemble_quad(int elem, const AsmParams &P, int64_t ngroups, h
 // gradients fit LDS.
 bool assemble_point_fits(int elem, int64_t stage, int kmax, int max_items);
 hipError_t launch_assemble_point(int elem, const AsmParams &P, int64_t ngroups, hipStream_t st);
+// Q2 hexahedra by row groups (HostPlan::rg_*), no element matrices in memory;
+// FP64, no Dirichlet rows.  geo: [n_cells][27][10], made once per pattern.
+struct Hex27Params {
+    const int32_t *info, *rows, *vis, *pairs, *ext;
+    const uint16_t *code;
+    const double *geo;
+    const double *rho;
+    double *K;
+    int n_groups, n_cu, window;  // window: set by the launcher
+    double E0, Emin, p;
+    int ip;
+    double lam, mu;
+};
+hipError_t launch_hex27_geometry(const int32_t *cells, const double *coords, int64_t n_cells, double *geo,
+                                 hipStream_t st);
+hipError_t launch_assemble_hex27(const Hex27Params &P, hipStream_t st);
 // elements per block (and per c partial) of the Q2 hexahedron's energy kernel;
 // the other elements take 256
 constexpr int kEnergyWideElems = 16;

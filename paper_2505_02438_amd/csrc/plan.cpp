@@ -8,6 +8,8 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <map>
+#include <mutex>
 #include <thread>
 #include <unordered_map>
 #include <unordered_set>
@@ -117,6 +119,189 @@ int general_table(const soptx_mesh *mesh, HostPlan &hp) {
         const int64_t b0 = hp.row_ptr[(size_t)(dim * n)] / d2;
         const int64_t deg = (hp.row_ptr[(size_t)(dim * n + 1)] - hp.row_ptr[(size_t)(dim * n)]) / dim;
         for (int64_t q = 0; q < deg; q++) hp.gnode[(size_t)(b0 + q)] = (int32_t)n;
+    }
+    return SOPTX_OK;
+}
+
+// ---- row groups of Q2 hexahedra (HostPlan::rg_*).  Every node belongs to one
+// of its elements, the one whose centroid lies furthest along a fixed oblique
+// direction: on a mesh of boxes, however numbered, an element then owns the
+// nodes of its lower corner (8 of 27), whose elements are it and its 7 lower
+// neighbours.  An element's nodes form one group, or several where the limits
+// of the kernel ask for it.
+struct RowGroups {
+    std::vector<int32_t> info, rows, vis, pairs, ext;
+    std::vector<uint16_t> code;
+};
+
+// the groups of one element's nodes own[0 .. n_own), appended to o; false if a
+// single node is over the limits
+bool element_row_groups(const soptx_mesh *mesh, const std::vector<int64_t> &n2e_ptr, const std::vector<int32_t> &n2e_e,
+                        const HostPlan &hp, const int32_t *own, int n_own, RowGroups &o) {
+    constexpr int nen = 27;
+    const int32_t *cells = mesh->cells;
+    int lat[nen], loc[nen];  // lattice index of a local node and back
+    for (int i = 0; i < nen; i++) {
+        lat[i] = lattice_index(i, 0) + 3 * lattice_index(i, 1) + 9 * lattice_index(i, 2);
+        loc[lat[i]] = i;
+    }
+    auto deg = [&](int32_t n) { return (hp.row_ptr[3 * (size_t)n + 1] - hp.row_ptr[3 * (size_t)n]) / 3; };
+    struct Row { int r, i; };
+    std::vector<std::vector<Row>> at;  // per visit its rows
+    std::vector<int32_t> vis, count, first;
+    std::vector<std::array<int32_t, 3>> term;  // a third or later term: block, place in code, position
+    for (int a = 0; a < n_own;) {
+        // the longest run of the nodes that fits
+        int b = n_own, np = 0;
+        for (;; b--) {
+            if (b == a) return false;
+            vis.clear();
+            int64_t stage = 0;
+            bool fits = b - a <= kRgRows;
+            for (int k = a; k < b; k++) {
+                const int32_t n = own[k];
+                vis.insert(vis.end(), n2e_e.begin() + n2e_ptr[n], n2e_e.begin() + n2e_ptr[n + 1]);
+                stage += 9 * deg(n);
+                fits = fits && deg(n) < 1365;  // 3 deg in 12 bits
+            }
+            std::sort(vis.begin(), vis.end());
+            vis.erase(std::unique(vis.begin(), vis.end()), vis.end());
+            if (!fits || (int)vis.size() > kRgVisits || stage > kRgStage) continue;
+            np = 0;
+            at.assign(vis.size(), {});
+            for (size_t v = 0; v < vis.size(); v++) {
+                for (int k = a; k < b; k++)
+                    for (int i = 0; i < nen; i++)
+                        if (cells[(int64_t)vis[v] * nen + i] == own[k]) at[v].push_back({k - a, i});
+                np += (int)(at[v].size() + 1) / 2;
+            }
+            // the terms of every block
+            first.clear();
+            int nb = 0, slots = 0, many = 0;
+            for (int k = a; k < b; k++) {
+                first.push_back(nb);
+                nb += deg(own[k]);
+            }
+            count.assign((size_t)nb, 0);
+            for (size_t v = 0; v < vis.size(); v++)
+                for (const Row &r : at[v])
+                    for (int j = 0; j < nen; j++) {
+                        const int c = ++count[(size_t)(first[(size_t)r.r] +
+                                                       hp.pos[((size_t)vis[v] * nen + r.i) * nen + j])];
+                        slots += c > 2;
+                        many += c == 3;
+                    }
+            if (np <= kRgPairs && many <= kRgExt && stage + 9 * slots <= kRgStage) break;
+        }
+        const size_t row0 = o.rows.size(), pair0 = o.pairs.size() / 2;
+        const size_t ext0 = o.ext.size();
+        int stage = 0;
+        for (int k = a; k < b; k++) {
+            const int32_t n = own[k];
+            const int32_t row[4] = {hp.row_ptr[3 * (size_t)n], deg(n), stage, n};
+            o.rows.insert(o.rows.end(), row, row + 4);
+            stage += 9 * deg(n);
+        }
+        o.rows.resize(row0 + 4 * kRgRows, 0);
+        o.vis.insert(o.vis.end(), vis.begin(), vis.end());
+        o.vis.resize((o.vis.size() + kRgVisits - 1) / kRgVisits * kRgVisits, vis[0]);
+        std::fill(count.begin(), count.end(), 0);
+        term.clear();
+        for (size_t v = 0; v < vis.size(); v++)
+            for (size_t k = 0; k < at[v].size(); k += 2) {
+                const bool two = k + 1 < at[v].size();
+                const Row r0 = at[v][k], r1 = two ? at[v][k + 1] : r0;
+                o.pairs.push_back((int32_t)v | lat[r0.i] << 8 | (two ? lat[r1.i] : 255) << 16);
+                o.pairs.push_back(r0.r | r1.r << 16);
+                for (int h = 0; h < 2; h++)
+                    for (int l = 0; l < nen; l++) {
+                        if (h == 1 && !two) {
+                            o.code.push_back(0);
+                            continue;
+                        }
+                        const Row &r = h ? r1 : r0;
+                        const int p = hp.pos[((size_t)vis[v] * nen + r.i) * nen + loc[l]];
+                        const int blk = first[(size_t)r.r] + p;
+                        const int rank = count[(size_t)blk]++;
+                        if (rank > 1) term.push_back({blk, (int32_t)o.code.size(), p});
+                        o.code.push_back((uint16_t)(p | (rank == 1 ? kRgSecond : 0)));
+                    }
+            }
+        std::sort(term.begin(), term.end());  // by block, then in visit order
+        for (size_t t = 0; t < term.size(); t++) {
+            o.code[(size_t)term[t][1]] = (uint16_t)(kRgSlot | (int)t);
+            if (t == 0 || term[t][0] != term[t - 1][0]) {
+                int r = b - a - 1;
+                while (first[(size_t)r] > term[t][0]) r--;
+                o.ext.push_back(o.rows[row0 + 4 * r + 2] + 3 * term[t][2]);
+                o.ext.push_back(3 * o.rows[row0 + 4 * r + 1] | (int32_t)t << 12);
+            }
+            o.ext.back() += 1 << 24;
+        }
+        const int32_t info[4] = {b - a, np, stage, (int32_t)((o.ext.size() - ext0) / 2)};
+        o.ext.resize(ext0 + 2 * kRgExt, 0);
+        o.pairs.resize(2 * (pair0 + kRgPairs), 0);
+        o.code.resize((pair0 + kRgPairs) * 2 * nen, 0);
+        o.info.insert(o.info.end(), info, info + 4);
+        a = b;
+    }
+    return true;
+}
+
+int row_groups(const soptx_mesh *mesh, const std::vector<int64_t> &n2e_ptr, const std::vector<int32_t> &n2e_e,
+               HostPlan &hp) {
+    constexpr int nen = 27;
+    const int64_t NN = hp.n_nodes, NC = hp.n_cells;
+    std::vector<double> along((size_t)NC);
+    for (int64_t e = 0; e < NC; e++) {
+        double t = 0.0;
+        for (int i = 0; i < 8; i++) {
+            const double *x = mesh->coords + 3 * (int64_t)mesh->cells[e * nen + i];
+            t += x[0] + 0.9 * x[1] + 0.8 * x[2];
+        }
+        along[(size_t)e] = t;
+    }
+    std::vector<int32_t> owner((size_t)NN, -1);
+    std::vector<int64_t> own_ptr((size_t)NC + 1, 0);
+    for (int64_t n = 0; n < NN; n++) {
+        for (int64_t s = n2e_ptr[n]; s < n2e_ptr[n + 1]; s++)
+            if (owner[n] < 0 || along[n2e_e[s]] > along[owner[n]]) owner[n] = n2e_e[s];
+        if (owner[n] >= 0) own_ptr[owner[n] + 1]++;
+    }
+    for (int64_t e = 0; e < NC; e++) own_ptr[e + 1] += own_ptr[e];
+    std::vector<int32_t> own((size_t)own_ptr[NC]);
+    {
+        std::vector<int64_t> fill(own_ptr.begin(), own_ptr.end() - 1);
+        for (int64_t n = 0; n < NN; n++)
+            if (owner[n] >= 0) own[fill[owner[n]]++] = (int32_t)n;
+    }
+    // ranges of elements in parallel, joined in order
+    std::map<int64_t, RowGroups> parts;
+    std::mutex mu;
+    std::atomic<bool> fits{true};
+    if (!parallel_for(NC, [&](int64_t a0, int64_t a1) {
+        RowGroups o;
+        for (int64_t e = a0; e < a1 && fits; e++)
+            if (own_ptr[e] < own_ptr[e + 1] &&
+                !element_row_groups(mesh, n2e_ptr, n2e_e, hp, own.data() + own_ptr[e],
+                                    (int)(own_ptr[e + 1] - own_ptr[e]), o))
+                fits = false;
+        std::lock_guard<std::mutex> lk(mu);
+        parts[a0] = std::move(o);
+    }))
+        return SOPTX_E_OOM;
+    size_t ncode = 0;
+    for (const auto &kv : parts) ncode += kv.second.code.size();
+    // the kernel's offsets are 32-bit; without row groups the element-matrix form runs
+    if (!fits || ncode >= (size_t)INT32_MAX) return SOPTX_OK;
+    for (const auto &kv : parts) {
+        const RowGroups &o = kv.second;
+        hp.rg_info.insert(hp.rg_info.end(), o.info.begin(), o.info.end());
+        hp.rg_rows.insert(hp.rg_rows.end(), o.rows.begin(), o.rows.end());
+        hp.rg_vis.insert(hp.rg_vis.end(), o.vis.begin(), o.vis.end());
+        hp.rg_pairs.insert(hp.rg_pairs.end(), o.pairs.begin(), o.pairs.end());
+        hp.rg_ext.insert(hp.rg_ext.end(), o.ext.begin(), o.ext.end());
+        hp.rg_code.insert(hp.rg_code.end(), o.code.begin(), o.code.end());
     }
     return SOPTX_OK;
 }
@@ -501,6 +686,7 @@ int build_host_plan(const soptx_mesh *mesh, HostPlan &hp, bool general) {
                 }
         }))
             return SOPTX_E_OOM;
+        if ((rc = row_groups(mesh, n2e_ptr, n2e_e, hp))) return rc;
         return general_table(mesh, hp);
     }
 

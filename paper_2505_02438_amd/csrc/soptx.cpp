@@ -166,6 +166,11 @@ struct soptx_pattern_s {
     double *coords = nullptr;
     int32_t *gptr = nullptr, *gent = nullptr, *gnode = nullptr;
     double *qgeo = nullptr;  // general Q1: per-point geometry of the row-block kernels
+    // Q2 hexahedra: row groups and per-point geometry of the fused assembly
+    int32_t *rg_info = nullptr, *rg_rows = nullptr, *rg_vis = nullptr, *rg_pairs = nullptr, *rg_ext = nullptr;
+    uint16_t *rg_code = nullptr;
+    double *geo27 = nullptr;
+    int64_t n_row_groups = 0;
     int max_items = 0;       // largest number of work items of a signature
     float *qgrad32 = nullptr;
     soptx_pattern_stats stats{};
@@ -366,6 +371,25 @@ static int build_pattern(const soptx_mesh *mesh, int32_t ref_method, bool genera
                 return rc;
             }
         }
+        if (!hp.rg_info.empty()) {
+            if ((rc = upload(h, hp.rg_info, &h->rg_info, st)) || (rc = upload(h, hp.rg_rows, &h->rg_rows, st)) ||
+                (rc = upload(h, hp.rg_vis, &h->rg_vis, st)) || (rc = upload(h, hp.rg_pairs, &h->rg_pairs, st)) ||
+                (rc = upload(h, hp.rg_code, &h->rg_code, st)) || (rc = upload(h, hp.rg_ext, &h->rg_ext, st))) {
+                free_handle(h);
+                return rc;
+            }
+            void *p = nullptr;
+            const size_t bytes = (size_t)hp.n_cells * 27 * 10 * sizeof(double);
+            if (hipMalloc(&p, bytes) != hipSuccess) { free_handle(h); return SOPTX_E_OOM; }
+            h->allocs.push_back(p);
+            h->stats.device_bytes += (int64_t)bytes;
+            h->geo27 = static_cast<double *>(p);
+            if (launch_hex27_geometry(h->cells, h->coords, hp.n_cells, h->geo27, st) != hipSuccess) {
+                free_handle(h);
+                return SOPTX_E_DEVICE;
+            }
+            h->n_row_groups = (int64_t)hp.rg_info.size() / 4;
+        }
         if (hipStreamSynchronize(st) != hipSuccess) { free_handle(h); return SOPTX_E_DEVICE; }
         const int64_t ncontrib = hp.n_cells * (int64_t)nen * nen;
         h->stats.ndof = hp.ndof; h->stats.nnz = hp.nnz; h->stats.n_cells = hp.n_cells; h->stats.n_nodes = hp.n_nodes;
@@ -403,9 +427,11 @@ static std::atomic<int> g_general_variant{-1};
 
 // the form of soptx_assemble_general on this handle: 1 = in LDS with the
 // blocks' sums in registers (k_assemble_point), 2 = in LDS with the sums in
-// the stage (k_assemble_quad), 0 = element matrices through memory
+// the stage (k_assemble_quad), 3 = Q2 hexahedra by row groups
+// (k_assemble_hex27), 0 = element matrices through memory
 static int general_form(soptx_pattern h) {
     const int v = g_general_variant.load();
+    if (h->n_row_groups > 0 && v != 0) return 3;
     if (!h->qgeo || v == 0) return 0;
     if (v != 1 && assemble_point_fits(h->elem, h->stage, h->kmax, h->max_items)) return 1;
     if (assemble_quad_fits(h->elem, h->stage, h->kmax)) return 2;
@@ -425,7 +451,15 @@ int soptx_assemble_general(soptx_pattern h, const soptx_material *m, const doubl
     if (!dg.ok) return SOPTX_E_DEVICE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int form = general_form(h);
-    if (form) {
+    if (form == 3) {
+        Hex27Params P{};
+        P.info = h->rg_info; P.rows = h->rg_rows; P.vis = h->rg_vis; P.pairs = h->rg_pairs; P.ext = h->rg_ext;
+        P.code = h->rg_code; P.geo = h->geo27; P.rho = d_rho; P.K = d_K_vals;
+        P.n_groups = (int)h->n_row_groups; P.n_cu = h->n_cu;
+        P.E0 = m->E0; P.Emin = m->Emin; P.p = m->p; P.ip = int_exponent(m->p);
+        lame(h, m, &P.lam, &P.mu);
+        if (launch_assemble_hex27(P, st) != hipSuccess) return SOPTX_E_DEVICE;
+    } else if (form) {
         AsmParams P{};
         if ((rc = asm_params(h, m, d_rho, d_K_vals, kF64, st, P))) return rc;
         P.qgeo = h->qgeo;
@@ -1011,6 +1045,7 @@ int soptx_debug_host_plan_array(soptx_host_plan p, const char *name, const void 
     SOPTX_ARR(pos)
     SOPTX_ARR(nb_tslot) SOPTX_ARR(nb_tdeg)
     SOPTX_ARR(gptr) SOPTX_ARR(gent) SOPTX_ARR(gnode) SOPTX_ARR(qgeo)
+    SOPTX_ARR(rg_info) SOPTX_ARR(rg_rows) SOPTX_ARR(rg_vis) SOPTX_ARR(rg_pairs) SOPTX_ARR(rg_code) SOPTX_ARR(rg_ext)
 #undef SOPTX_ARR
     return SOPTX_E_INVALID_ARG;
 }
