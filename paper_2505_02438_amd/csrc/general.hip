@@ -422,94 +422,159 @@ __global__ __launch_bounds__(256) void k_ke_general_wide(GenParams G) {
     }
 }
 
-// Element energies of Q2 hexahedra: kEnergyWideElems elements per block, each
-// of the 4 waves takes kEnergyWideElems / 4 of them in turn.  Per element the
-// node coordinates and displacements go to LDS, lane q < NQ forms the
-// point's term w_q |det J_q| (lambda tr(eps)^2 + 2 mu eps:eps) with the same
-// arithmetic as k_energy_general, and lane 0 adds the terms in ascending q.
+// Element energies of Q2 hexahedra: kEnergyWideElems elements per block, nine
+// at a time, a thread per (element, Gauss point): the point's term w_q |det J_q|
+// (lambda tr(eps)^2 + 2 mu eps:eps) with J and the reference gradient of u by
+// the tensor product (per line of three nodes along x the two sums of f and f'
+// of the six coordinates and displacements, then the line's factors along y
+// and z), then one thread per element adds the 27 terms in ascending q.
+// 24,000 elements: 30 us, against 60 with one element per wave (27 of 64 lanes,
+// the gradients of every node read per point).
 // Block partials: the block's element terms E s_e in ascending element
 // order, and f^T u as in k_energy_general.
-template <int NEN, int NQ>
-__global__ __launch_bounds__(256) void k_energy_general_wide(GenEnergyParams P) {
-    constexpr int DIM = 3, EPB = kEnergyWideElems, PER_WAVE = EPB / 4;
+__device__ constexpr double lag3(int k, double t) {
+    return k == 0 ? (1.0 - t) * (1.0 - 2.0 * t) : k == 1 ? 4.0 * t * (1.0 - t) : t * (2.0 * t - 1.0);
+}
+__device__ constexpr double dlag3(int k, double t) {
+    return k == 0 ? 4.0 * t - 3.0 : k == 1 ? 4.0 - 8.0 * t : 4.0 * t - 1.0;
+}
+constexpr int kEnergySet = 9;  // elements at a time
+static_assert(kEnergyWideElems % kEnergySet == 0 && kEnergySet * 27 <= 256, "a thread per (element, point)");
+
+__global__ __launch_bounds__(256) void k_energy_hex27(GenEnergyParams P) {
+    constexpr int EPB = kEnergyWideElems, NEN = 27, NQ = 27;
+    typedef double d2 __attribute__((ext_vector_type(2)));
     __shared__ double red[256];
     __shared__ double cp[EPB];
-    __shared__ double nx[4][NEN][2 * DIM];  // per wave: x then u of each node
-    __shared__ double sv[4][NQ];
-    const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-    for (int it = 0; it < PER_WAVE; it++) {
-        const int el = w * PER_WAVE + it;
-        const int64_t e = (int64_t)blockIdx.x * EPB + el;
-        const bool live = e < P.n_cells;
-        if (live && lane < NEN) {
-            const int64_t nd = P.cells[e * NEN + lane];
+    __shared__ d2 nx[kEnergySet][NEN][3];  // x then u of a node, by lattice index a + 3 b + 9 c
+    __shared__ double sv[kEnergySet][NQ];
+    __shared__ double tl[3][3], td[3][3];  // basis and derivative [node][point]
+    const int tid = threadIdx.x;
+    constexpr double r35 = 0.77459666924148337703585307995648;  // sqrt(3/5)
+    if (tid < 9) {
+        double v = 0.0, d = 0.0;
 #pragma unroll
-            for (int a = 0; a < DIM; a++) {
-                nx[w][lane][a] = P.coords[nd * DIM + a];
-                nx[w][lane][DIM + a] = P.u[nd * DIM + a];
+        for (int x = 0; x < 9; x++)
+            if (x == tid) {
+                v = lag3(x / 3, 0.5 * (1.0 + (x % 3 - 1) * r35));
+                d = dlag3(x / 3, 0.5 * (1.0 + (x % 3 - 1) * r35));
             }
+        tl[tid / 3][tid % 3] = v;
+        td[tid / 3][tid % 3] = d;
+    }
+    const int el = tid / NQ, q = tid - el * NQ;  // and the node this thread fetches
+    const int q0 = q % 3, q1 = q / 3 % 3, q2 = q / 9;
+    // lattice index of local node q: the 8 corners, then the others in ascending order
+    int lat = 0;
+    if (q < 8) {
+        lat = 2 * ((q ^ (q >> 1)) & 1) + 3 * (q & 2) + 9 * ((q & 4) / 2);
+    } else {
+        int n = q - 8;
+        for (int s = 0; s < 27; s++) {
+            const bool odd = s % 3 == 1 || s / 3 % 3 == 1 || s / 9 == 1;
+            if (odd && n-- == 0) lat = s;
+        }
+    }
+    for (int set = 0; set < EPB / kEnergySet; set++) {
+        const int64_t e = (int64_t)blockIdx.x * EPB + set * kEnergySet + el;
+        const bool live = el < kEnergySet && e < P.n_cells;
+        if (live) {
+            const int64_t nd = P.cells[e * NEN + q];
+            const double *c = P.coords + nd * 3, *u = P.u + nd * 3;
+            nx[el][lat][0] = d2{c[0], c[1]};
+            nx[el][lat][1] = d2{c[2], u[0]};
+            nx[el][lat][2] = d2{u[1], u[2]};
         }
         __syncthreads();
-        if (live && lane < NQ) {
-            const int q = lane;
-            double J[DIM][DIM], Hr[DIM][DIM];
+        if (live) {
+            double lx[3], dx[3], J[3][6];  // J[m][v]: derivative along xi_m of value v
 #pragma unroll
-            for (int a = 0; a < DIM; a++)
+            for (int k = 0; k < 3; k++) {
+                lx[k] = tl[k][q0];
+                dx[k] = td[k][q0];
+            }
 #pragma unroll
-                for (int m = 0; m < DIM; m++) J[a][m] = Hr[a][m] = 0.0;
-            for (int k = 0; k < NEN; k++)
+            for (int m = 0; m < 3; m++)
 #pragma unroll
-                for (int m = 0; m < DIM; m++) {
-                    const double gm = P.qgrad[(q * NEN + k) * DIM + m];
+                for (int v = 0; v < 6; v++) J[m][v] = 0.0;
 #pragma unroll
-                    for (int a = 0; a < DIM; a++) {
-                        J[a][m] += nx[w][k][a] * gm;
-                        Hr[a][m] += nx[w][k][DIM + a] * gm;
+            for (int z = 0; z < 3; z++) {
+                const double fz = tl[z][q2], dz = td[z][q2];
+#pragma unroll
+                for (int y = 0; y < 3; y++) {
+                    const double fy = tl[y][q1], dy = td[y][q1];
+                    const double A = fy * fz, B = dy * fz, C = fy * dz;
+                    double t[3][6];
+#pragma unroll
+                    for (int x = 0; x < 3; x++)
+#pragma unroll
+                        for (int v = 0; v < 3; v++) {
+                            const d2 p = nx[el][x + 3 * y + 9 * z][v];
+                            t[x][2 * v] = p.x;
+                            t[x][2 * v + 1] = p.y;
+                        }
+#pragma unroll
+                    for (int v = 0; v < 6; v++) {
+                        double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+                        for (int x = 0; x < 3; x++) {
+                            s0 = fma(dx[x], t[x][v], s0);
+                            s1 = fma(lx[x], t[x][v], s1);
+                        }
+                        J[0][v] = fma(A, s0, J[0][v]);
+                        J[1][v] = fma(B, s1, J[1][v]);
+                        J[2][v] = fma(C, s1, J[2][v]);
                     }
                 }
-            const double c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-            const double c01 = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-            const double c02 = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-            const double c10 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-            const double c11 = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-            const double c12 = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-            const double c20 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-            const double c21 = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-            const double c22 = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-            const double det = J[0][0] * c00 + J[0][1] * c10 + J[0][2] * c20;
+            }
+            // dx_a / dxi_m = J[m][a]
+            const double c00 = J[1][1] * J[2][2] - J[2][1] * J[1][2];
+            const double c01 = J[2][0] * J[1][2] - J[1][0] * J[2][2];
+            const double c02 = J[1][0] * J[2][1] - J[2][0] * J[1][1];
+            const double c10 = J[2][1] * J[0][2] - J[0][1] * J[2][2];
+            const double c11 = J[0][0] * J[2][2] - J[2][0] * J[0][2];
+            const double c12 = J[2][0] * J[0][1] - J[0][0] * J[2][1];
+            const double c20 = J[0][1] * J[1][2] - J[1][1] * J[0][2];
+            const double c21 = J[1][0] * J[0][2] - J[0][0] * J[1][2];
+            const double c22 = J[0][0] * J[1][1] - J[1][0] * J[0][1];
+            const double det = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
             const double id = 1.0 / det;
-            const double inv[DIM][DIM] = {{c00 * id, c01 * id, c02 * id},
-                                          {c10 * id, c11 * id, c12 * id},
-                                          {c20 * id, c21 * id, c22 * id}};
-            double H[DIM][DIM];
+            // d xi_m / d x_b
+            const double inv[3][3] = {{c00 * id, c01 * id, c02 * id},
+                                      {c10 * id, c11 * id, c12 * id},
+                                      {c20 * id, c21 * id, c22 * id}};
+            double H[3][3];
 #pragma unroll
-            for (int a = 0; a < DIM; a++)
+            for (int a = 0; a < 3; a++)
 #pragma unroll
-                for (int b = 0; b < DIM; b++) {
+                for (int b = 0; b < 3; b++) {
                     double t = 0.0;
 #pragma unroll
-                    for (int m = 0; m < DIM; m++) t += Hr[a][m] * inv[m][b];
+                    for (int m = 0; m < 3; m++) t += J[m][3 + a] * inv[m][b];
                     H[a][b] = t;
                 }
             double tr = 0.0, ee = 0.0;
 #pragma unroll
-            for (int a = 0; a < DIM; a++) {
+            for (int a = 0; a < 3; a++) {
                 tr += H[a][a];
 #pragma unroll
-                for (int b = 0; b < DIM; b++) {
+                for (int b = 0; b < 3; b++) {
                     const double eab = 0.5 * (H[a][b] + H[b][a]);
                     ee += eab * eab;
                 }
             }
-            sv[w][q] = P.qw[q] * fabs(det) * (P.lam * tr * tr + 2.0 * P.mu * ee);
+            const double w = (q0 == 1 ? 8.0 : 5.0) * (q1 == 1 ? 8.0 : 5.0) * (q2 == 1 ? 8.0 : 5.0) / 5832.0;
+            sv[el][q] = w * fabs(det) * (P.lam * tr * tr + 2.0 * P.mu * ee);
         }
         __syncthreads();
-        if (lane == 0) {
+        if (tid < kEnergySet) {
+            const int64_t es = (int64_t)blockIdx.x * EPB + set * kEnergySet + tid;
             double cpart = 0.0;
-            if (live) {
+            if (es < P.n_cells) {
                 double s = 0.0;
-                for (int q = 0; q < NQ; q++) s += sv[w][q];
-                const double r = P.rho[e];
+#pragma unroll
+                for (int k = 0; k < NQ; k++) s += sv[tid][k];
+                const double r = P.rho[es];
                 double rp1 = 1.0;  // rho^(p - 1)
                 if (P.ip >= 1) {
                     for (int k = 0; k < P.ip - 1; k++) rp1 *= r;
@@ -517,26 +582,25 @@ __global__ __launch_bounds__(256) void k_energy_general_wide(GenEnergyParams P) 
                     rp1 = general_pow(r, P.p - 1.0);
                 }
                 const double E = P.Emin + rp1 * r * (P.E0 - P.Emin);
-                if (P.dc) P.dc[e] = -P.p * rp1 * (P.E0 - P.Emin) * s;
+                if (P.dc) P.dc[es] = -P.p * rp1 * (P.E0 - P.Emin) * s;
                 cpart = E * s;
             }
-            cp[el] = cpart;
+            cp[set * kEnergySet + tid] = cpart;
         }
-        // the next element's LDS writes come after the next barrier, which
-        // lane 0 reaches only once it has read sv
+        // the next set's terms are written after its first barrier, which these threads reach then
     }
     if (!P.partials) return;
     double fpart = 0.0;
     if (P.f)
-        for (int64_t rr = (int64_t)blockIdx.x * 256 + threadIdx.x; rr < P.ndof; rr += (int64_t)gridDim.x * 256)
+        for (int64_t rr = (int64_t)blockIdx.x * 256 + tid; rr < P.ndof; rr += (int64_t)gridDim.x * 256)
             fpart += P.f[rr] * P.u[rr];
-    red[threadIdx.x] = fpart;
+    red[tid] = fpart;
     __syncthreads();
     for (int st = 128; st > 0; st >>= 1) {
-        if ((int)threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
+        if (tid < st) red[tid] += red[tid + st];
         __syncthreads();
     }
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
         double bc = 0.0;
         for (int k = 0; k < EPB; k++) bc += cp[k];
         P.partials[blockIdx.x] = bc;
@@ -544,11 +608,9 @@ __global__ __launch_bounds__(256) void k_energy_general_wide(GenEnergyParams P) 
     }
 }
 
-template <int NEN, int NQ>
-hipError_t launch_energy_wide(const GenEnergyParams &P, hipStream_t st) {
-    if (P.nq != NQ) return hipErrorInvalidValue;
+hipError_t launch_energy_hex27(const GenEnergyParams &P, hipStream_t st) {
     const unsigned g = (unsigned)((P.n_cells + kEnergyWideElems - 1) / kEnergyWideElems);
-    hipLaunchKernelGGL((k_energy_general_wide<NEN, NQ>), dim3(g > 0 ? g : 1), dim3(256), 0, st, P);
+    hipLaunchKernelGGL(k_energy_hex27, dim3(g > 0 ? g : 1), dim3(256), 0, st, P);
     return hipGetLastError();
 }
 
@@ -592,7 +654,7 @@ hipError_t launch_t(const GenParams &G, hipStream_t st) {
 
 hipError_t launch_energy_general(int elem, const GenEnergyParams &P, hipStream_t st) {
     if (elem == SOPTX_HEX8) return launch_energy_t<3, 8, 8>(P, st);
-    if (elem == SOPTX_HEX27) return launch_energy_wide<27, 27>(P, st);
+    if (elem == SOPTX_HEX27) return launch_energy_hex27(P, st);
     if (elem == SOPTX_QUAD4) return launch_energy_t<2, 4, 4>(P, st);
     return hipErrorInvalidValue;
 }

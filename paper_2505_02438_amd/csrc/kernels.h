@@ -205,7 +205,7 @@ hipError_t launch_hex27_geometry(const int32_t *cells, const double *coords, int
 hipError_t launch_assemble_hex27(const Hex27Params &P, hipStream_t st);
 // elements per block (and per c partial) of the Q2 hexahedron's energy kernel;
 // the other elements take 256
-constexpr int kEnergyWideElems = 16;
+constexpr int kEnergyWideElems = 18;
 // element energies with per-quadrature-point geometry: dc and block partials
 // of c and f^T u (as EnergyParams), FP64
 struct GenEnergyParams {
