@@ -107,6 +107,54 @@ __device__ __forceinline__ void wave_finalize(const double *partials, int n, int
 // than those of 8)
 typedef double Two __attribute__((ext_vector_type(2)));
 
+// The same for either arithmetic type: n values of type T.
+template <class T> struct Wide;
+template <> struct Wide<double> {
+    static constexpr int n = 2;
+    using V = Two;
+};
+template <> struct Wide<float> {
+    static constexpr int n = 4;
+    typedef float V __attribute__((ext_vector_type(4)));
+};
+// N values of every element slot in LDS: whole Wides slot by slot, then what is
+// left value by value.  Where value c of a slot lies, and all of a slot's.
+template <int N, class T>
+__device__ __forceinline__ int slot_at(int c, int slot) {
+    constexpr int n = Wide<T>::n;
+    return c < N / n * n ? c / n * n * kGroupElems + n * slot + c % n : c * kGroupElems + slot;
+}
+template <int N, class T>
+__device__ __forceinline__ void load_slot(const T *G, int slot, T (&v)[N]) {
+    constexpr int n = Wide<T>::n;
+#pragma unroll
+    for (int c = 0; c < N / n * n; c += n) {
+        const typename Wide<T>::V x = *reinterpret_cast<const typename Wide<T>::V *>(G + slot_at<N, T>(c, slot));
+#pragma unroll
+        for (int k = 0; k < n; k++) v[c + k] = x[k];
+    }
+#pragma unroll
+    for (int c = N / n * n; c < N; c++) v[c] = G[slot_at<N, T>(c, slot)];
+}
+// ROWS rows of N values the same way: whole Wides row by row, then the rest.
+template <int N, int ROWS, class T>
+__device__ __forceinline__ int row_at(int row, int c) {
+    constexpr int whole = N / Wide<T>::n * Wide<T>::n;
+    return c < whole ? row * whole + c : ROWS * whole + row * (N - whole) + c - whole;
+}
+template <int N, int ROWS, class T>
+__device__ __forceinline__ void load_row(const T *M, int row, T (&v)[N]) {
+    constexpr int n = Wide<T>::n;
+#pragma unroll
+    for (int c = 0; c < N / n * n; c += n) {
+        const typename Wide<T>::V x = *reinterpret_cast<const typename Wide<T>::V *>(M + row_at<N, ROWS, T>(row, c));
+#pragma unroll
+        for (int k = 0; k < n; k++) v[c + k] = x[k];
+    }
+#pragma unroll
+    for (int c = N / n * n; c < N; c++) v[c] = M[row_at<N, ROWS, T>(row, c)];
+}
+
 // eight consecutive wave-uniform int32 by one scalar load
 typedef int Codes8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ Codes8 ld_codes8(const int32_t *p) {
@@ -241,6 +289,12 @@ __device__ __forceinline__ void contribute_point(const double *Gs, int slot, int
 // (slot of element k of each node, [K][32]); ticket counts the group's work
 // items.  GEOM is decided once per group, so the contraction loop has no
 // branch on it.
+// A contribution reads its element's G' and its pair's M in 16-byte pieces
+// (slot_at, row_at): a 16-byte LDS read costs about the cycles of an 8-byte one,
+// and the loop is paced by its LDS reads.  In pieces of one value each: P2
+// tetrahedra 48^3 688 us per step (now 640 with the same waves), sheared Q1
+// hexahedra 87x41x37 in FP32 127 (now 125), P1 triangles 600x200 24.1 (now
+// 23.3).
 
 // ---- compute role, wide work items (groups of at most N = 8 or 16
 // nodes): lane = (pp Q + q) N + node takes position p[pp] of the item and
@@ -322,26 +376,26 @@ __device__ __forceinline__ void assemble_wide(const AsmParams &P, const int *hdr
                 if constexpr (GEOM > kGeoPoint) {
                     contribute_point<DIM, NEN, GEOM - kGeoPoint>(G, slot, i, j, true, acc);
                 } else {
-                    const T *Mij = sM + (i * NEN + j) * D2;
                     T Mv[D2];
-#pragma unroll
-                    for (int x = 0; x < D2; x++) Mv[x] = Mij[x];
+                    load_row<D2, NEN * NEN, T>(sM, i * NEN + j, Mv);
                     if constexpr (GEOM == kGeoDiag) {
-                        T dd[DIM][DIM];
+                        T dd[DIM][DIM], dg[DIM];
+                        load_slot<DIM, T>(G, slot, dg);
 #pragma unroll
                         for (int a = 0; a < DIM; a++)
 #pragma unroll
                             for (int c = a; c < DIM; c++) {
-                                dd[a][c] = diag_product<PREC>(G[a * kGroupElems + slot], G[c * kGroupElems + slot]);
+                                dd[a][c] = diag_product<PREC>(dg[a], dg[c]);
                                 dd[c][a] = dd[a][c];
                             }
                         accumulate_diag<DIM, PREC>(dd, Mv, acc);
                     } else {
-                        T Gv[DIM][DIM];
+                        T Gv[DIM][DIM], gf[D2];
+                        load_slot<D2, T>(G, slot, gf);
 #pragma unroll
                         for (int m = 0; m < DIM; m++)
 #pragma unroll
-                            for (int a = 0; a < DIM; a++) Gv[m][a] = G[(m * DIM + a) * kGroupElems + slot];
+                            for (int a = 0; a < DIM; a++) Gv[m][a] = gf[m * DIM + a];
                         accumulate<DIM, PREC>(Gv, Mv, acc);
                     }
                 }
@@ -466,26 +520,26 @@ __device__ __forceinline__ void assemble_pairs(const AsmParams &P, const int *hd
                 if constexpr (GEOM > kGeoPoint) {
                     contribute_point<DIM, NEN, GEOM - kGeoPoint>(G, slot, i, j, oku, acc);
                 } else {
-                    const T *Mij = sM + (i * NEN + j) * D2;
                     T Mv[D2];
-#pragma unroll
-                    for (int x = 0; x < D2; x++) Mv[x] = Mij[x];
+                    load_row<D2, NEN * NEN, T>(sM, i * NEN + j, Mv);
                     if constexpr (GEOM == kGeoDiag) {
-                        T dd[DIM][DIM];
+                        T dd[DIM][DIM], dg[DIM];
+                        load_slot<DIM, T>(G, slot, dg);
 #pragma unroll
                         for (int a = 0; a < DIM; a++)
 #pragma unroll
                             for (int c = a; c < DIM; c++) {
-                                dd[a][c] = diag_product<PREC>(G[a * kGroupElems + slot], G[c * kGroupElems + slot]);
+                                dd[a][c] = diag_product<PREC>(dg[a], dg[c]);
                                 dd[c][a] = dd[a][c];
                             }
                         if (oku) accumulate_diag<DIM, PREC>(dd, Mv, acc);
                     } else {
-                        T Gv[DIM][DIM];
+                        T Gv[DIM][DIM], gf[D2];
+                        load_slot<D2, T>(G, slot, gf);
 #pragma unroll
                         for (int m = 0; m < DIM; m++)
 #pragma unroll
-                            for (int a = 0; a < DIM; a++) Gv[m][a] = G[(m * DIM + a) * kGroupElems + slot];
+                            for (int a = 0; a < DIM; a++) Gv[m][a] = gf[m * DIM + a];
                         if (oku) accumulate<DIM, PREC>(Gv, Mv, acc);
                     }
                 }
@@ -660,16 +714,16 @@ __device__ __forceinline__ void store_rows(const AsmParams &P, const int *hdr, c
 // (slicing the whole group range per XCD instead spreads the writes over
 // eight distant stretches and is slower).
 // In step s:
-//   - compute waves (0..7) assemble group s into LDS stage s&1: each takes a
+//   - compute waves (Roles::comp) assemble group s into LDS stage s&1: each takes a
 //     pair of neighbour positions of the group's signature from a ticket
 //     (costliest first); the low half of the wave walks the first position's
 //     contributions, the high half the second's, lane = node of the group;
 //     a finished DIM x DIM block goes to the node's row block in the stage;
-//   - store waves (8..11) write group s-1 from stage (s-1)&1: every node's
+//   - store waves (Roles::store) write group s-1 from stage (s-1)&1: every node's
 //     DIM rows are contiguous in CSR and go out as one run.  They issue
 //     stores only and never wait for them, so the CU's stores stream while
 //     the next groups are computed;
-//   - load waves (12..15) load group s+1 (G' = sqrt(E(rho) det J) J^-1, or
+//   - load waves (the last 4) load group s+1 (G' = sqrt(E(rho) det J) J^-1, or
 //     for an axis-aligned group its diagonal G'_aa, the slot table and the
 //     row offsets) into the other LDS buffers.  They load only, so their
 //     waits cover their own loads and none of the stores.
@@ -687,11 +741,12 @@ __device__ __forceinline__ void store_rows(const AsmParams &P, const int *hdr, c
 constexpr int kAsmThreads = 1024;
 constexpr int kLoadWaves = 4;
 // compute and store waves of the persistent kernel (with the 4 load waves, 16
-// in all): P2 tetrahedra, whose steps are paced by the compute waves, take
-// two waves from the store role
+// in all): P2 tetrahedra, whose steps the compute waves pace as often as the
+// stores, take one wave from the store role (step of the 48^3 box: 628 us with
+// 8 compute waves, 618 with 9, 638 with 10)
 template <int NEN>
 struct Roles {
-    static constexpr int comp = NEN == 10 ? 10 : 8;
+    static constexpr int comp = NEN == 10 ? 9 : 8;
     static constexpr int store = kAsmThreads / 64 - kLoadWaves - comp;
 };
 static_assert(2 * kGroupNodes == 64, "two positions per wavefront");
@@ -710,8 +765,8 @@ __global__ __launch_bounds__(kAsmThreads, 1) void k_assemble(AsmParams P) {
     static_assert(2 * NG <= kSetThreads, "row offsets: one per load thread");
     extern __shared__ __align__(16) unsigned char smem[];
     double *stage = reinterpret_cast<double *>(smem);                      // [2][P.stage]
-    T *sG = reinterpret_cast<T *>(stage + 2 * P.stage);                     // [2][D2][kGroupElems]
-    T *sM = sG + 2 * D2 * kGroupElems;                                      // [NEN][NEN][D2]
+    T *sG = reinterpret_cast<T *>(stage + 2 * P.stage);                     // [2][D2 kGroupElems], slot_at
+    T *sM = sG + 2 * D2 * kGroupElems;                                      // [NEN NEN D2], row_at
     int32_t *srows = reinterpret_cast<int32_t *>(sM + NEN * NEN * D2);      // [3][NG][2]
     uint16_t *sn2l = reinterpret_cast<uint16_t *>(srows + 3 * NG * 2);      // [2][kmax][NG]
     __shared__ int ticket[2];
@@ -733,10 +788,8 @@ __global__ __launch_bounds__(kAsmThreads, 1) void k_assemble(AsmParams P) {
     const int nsteps = (ngr - 1 - g0) / stride + 2;  // groups of this workgroup, plus the last store step
     const int n2l_stride = P.kmax * NG;
 
-    for (int x = tid; x < NEN * NEN * D2; x += kAsmThreads) {
-        if (PREC == kF64) sM[x] = (T)P.M[x];
-        else sM[x] = (T)P.M32[x];
-    }
+    for (int x = tid; x < NEN * NEN * D2; x += kAsmThreads)
+        sM[row_at<D2, NEN * NEN, T>(x / D2, x % D2)] = PREC == kF64 ? (T)P.M[x] : (T)P.M32[x];
 
     // ---- load role: two sets of kLoadWaves / 2 waves; set x puts the groups
     // of the steps of parity x and has two steps to bring each one in.  A
@@ -807,10 +860,10 @@ __global__ __launch_bounds__(kAsmThreads, 1) void k_assemble(AsmParams P) {
                     // the diagonal G'_aa only; the compute waves form the
                     // products G'_aa G'_cc
 #pragma unroll
-                    for (int a = 0; a < DIM; a++) G[a * kGroupElems + slot] = (T)(qq * q.pd[h][a * DIM + a]);
+                    for (int a = 0; a < DIM; a++) G[slot_at<DIM, T>(a, slot)] = (T)(qq * q.pd[h][a * DIM + a]);
                 } else {
 #pragma unroll
-                    for (int c = 0; c < D2; c++) G[c * kGroupElems + slot] = (T)(qq * q.pd[h][c]);
+                    for (int c = 0; c < D2; c++) G[slot_at<D2, T>(c, slot)] = (T)(qq * q.pd[h][c]);
                 }
             }
         }
@@ -912,8 +965,8 @@ __global__ __launch_bounds__(OsShape<DIM>::threads) void k_assemble_os(AsmParams
     constexpr int kStoreWaves = kOsThreads / 64;
     extern __shared__ __align__(16) unsigned char smem[];
     double *stage = reinterpret_cast<double *>(smem);                  // [P.stage]
-    T *sG = reinterpret_cast<T *>(stage + P.stage);                     // [D2][kGroupElems]
-    T *sM = sG + D2 * kGroupElems;                                      // [NEN][NEN][D2]
+    T *sG = reinterpret_cast<T *>(stage + (P.stage + 1) / 2 * 2);       // [D2 kGroupElems], slot_at
+    T *sM = sG + D2 * kGroupElems;                                      // [NEN NEN D2], row_at
     int32_t *srows = reinterpret_cast<int32_t *>(sM + NEN * NEN * D2);  // [NG][2]
     uint16_t *sn2l = reinterpret_cast<uint16_t *>(srows + NG * 2);      // [kmax][NG]
     __shared__ int ticket;
@@ -938,10 +991,8 @@ __global__ __launch_bounds__(OsShape<DIM>::threads) void k_assemble_os(AsmParams
     const int n2off = wave_uniform(ldc(P.grp_info, kGrpInfo * gg + 4));
     const int gflags = wave_uniform(ldc(P.grp_info, kGrpInfo * gg + 5));
     const int nk = wave_uniform(ldc(P.sig_info, 4 * sg + 0)) * NG;
-    for (int x = tid; x < NEN * NEN * D2; x += kOsThreads) {
-        if (PREC == kF64) sM[x] = (T)P.M[x];
-        else sM[x] = (T)P.M32[x];
-    }
+    for (int x = tid; x < NEN * NEN * D2; x += kOsThreads)
+        sM[row_at<D2, NEN * NEN, T>(x / D2, x % D2)] = PREC == kF64 ? (T)P.M[x] : (T)P.M32[x];
     // two slots per thread and pass, their loads in flight together (a group
     // can hold a few more elements than the workgroup has threads)
     for (int s0 = tid; s0 < ne; s0 += 2 * kOsThreads) {
@@ -974,10 +1025,10 @@ __global__ __launch_bounds__(OsShape<DIM>::threads) void k_assemble_os(AsmParams
                 const double qq = sqrt(E * gd[h][D2]);
                 if (gflags & kGrpDiag) {
 #pragma unroll
-                    for (int a = 0; a < DIM; a++) sG[a * kGroupElems + slot] = (T)(qq * gd[h][a * DIM + a]);
+                    for (int a = 0; a < DIM; a++) sG[slot_at<DIM, T>(a, slot)] = (T)(qq * gd[h][a * DIM + a]);
                 } else {
 #pragma unroll
-                    for (int c = 0; c < D2; c++) sG[c * kGroupElems + slot] = (T)(qq * gd[h][c]);
+                    for (int c = 0; c < D2; c++) sG[slot_at<D2, T>(c, slot)] = (T)(qq * gd[h][c]);
                 }
             }
     }
@@ -2350,8 +2401,8 @@ template <int DIM, int NEN, int PREC, bool FUSE>
 static hipError_t launch_assemble_os_t(const AsmParams &P0, int64_t ngroups, hipStream_t st) {
     if (ngroups <= 0) return hipSuccess;
     const size_t csz = PREC == kF64 ? 8 : 4;
-    const size_t lds = 8 * (size_t)P0.stage + csz * DIM * DIM * kGroupElems + csz * NEN * NEN * DIM * DIM +
-                       kGroupNodes * 2 * 4 + 2 * (size_t)P0.kmax * kGroupNodes;
+    const size_t lds = 8 * (size_t)((P0.stage + 1) / 2 * 2) + csz * DIM * DIM * kGroupElems +
+                       csz * NEN * NEN * DIM * DIM + kGroupNodes * 2 * 4 + 2 * (size_t)P0.kmax * kGroupNodes;
     if (lds + 64 > 160 * 1024) return hipErrorInvalidValue;
     const void *fn = reinterpret_cast<const void *>(&k_assemble_os<DIM, NEN, PREC, FUSE>);
     static std::mutex mu;
