@@ -185,7 +185,7 @@ hipError_t launch_assemble_quad(int elem, const AsmParams &P, int64_t ngroups, h
 // plans whose signatures have at most a fixed number of work items
 // (max_items: the largest over the plan's signatures) and whose stage and
 // gradients fit LDS.
-bool assemble_point_fits(int elem, int64_t stage, int kmax, int max_items);
+bool assemble_point_fits(int elem, int64_t n_cells, int64_t stage, int kmax, int max_items);
 hipError_t launch_assemble_point(int elem, const AsmParams &P, int64_t ngroups, hipStream_t st);
 // Q2 hexahedra by row groups (HostPlan::rg_*), no element matrices in memory;
 // FP64, no Dirichlet rows.  geo: [n_cells][27][10], made once per pattern.

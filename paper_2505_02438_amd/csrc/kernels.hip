@@ -1236,62 +1236,130 @@ __global__ __launch_bounds__(QuadShape<DIM>::threads) void k_assemble_quad(AsmPa
 // the lane layout are those of assemble_pairs / assemble_wide; a split
 // position's two halves, and a wide item's phases, are added at the end.
 
-// Pairs item r (r <= deg): this pass's terms of the lane's contributions
-// into acc; with fin (after the last pass), the halves are added and the
-// lane's block goes to its row block in the stage.
+// The kernel's gradients in LDS: the slots' first two components side by side
+// per (point qq of the pass, node k), then (3D) all third ones; both lie at
+// multiples of one index, entry = (qq NEN + k) kGroupElems + slot.
 template <int DIM, int NEN, int QP>
-__device__ __forceinline__ void point_pairs(const AsmParams &P, const int *hdr, int r, const double *Gs,
-                                            const uint16_t *sn2l, int lane, double *stage, bool fin,
+__device__ __forceinline__ void put_gradient(double *sg, int entry, const double (&g)[DIM]) {
+    reinterpret_cast<Two *>(sg)[entry] = Two{g[0], g[1]};
+    if constexpr (DIM == 3) sg[2 * QP * NEN * kGroupElems + entry] = g[2];
+}
+// acc += g_i g_j^T over the pass's points; ei, ej: the entries at its first point
+template <int DIM, int NEN, int QP>
+__device__ __forceinline__ void contribute_entries(const double *sg, int ei, int ej, bool ok, double (&acc)[DIM][DIM]) {
+    const Two *xy = reinterpret_cast<const Two *>(sg);
+    const double *z = sg + 2 * QP * NEN * kGroupElems;
+#pragma unroll
+    for (int q = 0; q < QP; q++) {
+        constexpr int step = NEN * kGroupElems;
+        const Two vi = xy[ei + q * step], vj = xy[ej + q * step];
+        double gi[DIM], gj[DIM];
+        gi[0] = vi.x;
+        gi[1] = vi.y;
+        gj[0] = vj.x;
+        gj[1] = vj.y;
+        if constexpr (DIM == 3) {
+            gi[2] = z[ei + q * step];
+            gj[2] = z[ej + q * step];
+        }
+        if (ok) {
+#pragma unroll
+            for (int a = 0; a < DIM; a++)
+#pragma unroll
+                for (int c = 0; c < DIM; c++) acc[a][c] = fma(gi[a], gj[c], acc[a][c]);
+        }
+    }
+}
+
+// One pairs item, read once for all passes: its positions, the contribution
+// lists of the two halves
+struct PairItem {
+    int pa, pb, lo0, nlo, hi0, nhi;
+    __device__ __forceinline__ bool split() const { return pb == pa; }
+};
+__device__ __forceinline__ void read_pair(const AsmParams &P, int posoff, int r, PairItem &it) {
+    it.pa = ldc(P.sig_pairs, 2 * posoff + 2 * r);
+    it.pb = ldc(P.sig_pairs, 2 * posoff + 2 * r + 1);
+    it.lo0 = it.nlo = it.hi0 = it.nhi = 0;
+    if (it.pa < 0) return;
+    const int c0 = ldc(P.sig_pos_ptr, posoff + it.pa);
+    const int na = ldc(P.sig_pos_ptr, posoff + it.pa + 1) - c0;
+    it.lo0 = it.hi0 = c0;
+    it.nlo = na;
+    if (it.split()) {
+        it.nlo = (na + 1) / 2;
+        it.hi0 = c0 + it.nlo;
+        it.nhi = na - it.nlo;
+    } else if (it.pb >= 0) {
+        const int h0 = ldc(P.sig_pos_ptr, posoff + it.pb);
+        it.nhi = ldc(P.sig_pos_ptr, posoff + it.pb + 1) - h0;
+        if (it.nhi > 0) it.hi0 = h0;
+    }
+}
+
+// a pass's terms of the lane's contributions of the item into acc; kept: the
+// entries (ei | ej << 16) of the first kKept contributions, found in the first pass
+template <int DIM, int NEN, int QP, int kKept>
+__device__ __forceinline__ void point_pairs(const AsmParams &P, const PairItem &it, int (&kept)[kKept], bool first,
+                                            const double *sg, const uint16_t *sn2l, int lane,
                                             double (&acc)[DIM][DIM]) {
     constexpr int NG = kGroupNodes;
+    const bool hi = lane >= NG;
+    const uint16_t *n2l = sn2l + (lane & (NG - 1));
+    const int mycnt = hi ? it.nhi : it.nlo;
+    const int32_t *lo_p = P.sig_contrib + it.lo0;
+    const int32_t *hi_p = P.sig_contrib + it.hi0;
+    auto entries = [&](int lo, int hi_, bool ok) {
+        const int code = ok ? (hi ? hi_ : lo) : 0;
+        const int slot = n2l[(code >> 16) * NG];
+        return (((code >> 8) & 255) * kGroupElems + slot) | (((code & 255) * kGroupElems + slot) << 16);
+    };
+    if (first) {
+        const Codes8 cl = ld_codes8(lo_p), ch = ld_codes8(hi_p);
+#pragma unroll
+        for (int u = 0; u < kKept; u++) kept[u] = entries(cl[u], ch[u], u < mycnt);
+    }
+#pragma unroll
+    for (int u = 0; u < kKept; u++) {
+        if (u >= it.nlo) break;
+        contribute_entries<DIM, NEN, QP>(sg, kept[u] & 0xffff, kept[u] >> 16, u < mycnt, acc);
+    }
+    if (it.nlo <= kKept) return;
+    // longer lists (nodes of more than eight elements): the rest of the codes
+    // anew in every pass
+    for (int t0 = 0; t0 < it.nlo; t0 += 8) {
+        const Codes8 cl = ld_codes8(lo_p + t0), ch = ld_codes8(hi_p + t0);
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            if (t0 + u >= it.nlo) break;
+            if (t0 + u < kKept) continue;
+            const bool oku = t0 + u < mycnt;
+            const int e = entries(cl[u], ch[u], oku);
+            contribute_entries<DIM, NEN, QP>(sg, e & 0xffff, e >> 16, oku, acc);
+        }
+    }
+}
+
+// after the last pass: the halves are added and the lane's block goes to its
+// row block in the stage
+template <int DIM>
+__device__ __forceinline__ void finish_pairs(const AsmParams &P, const int *hdr, const PairItem &it, int lane,
+                                             double *stage, double (&acc)[DIM][DIM]) {
+    constexpr int NG = kGroupNodes;
+    if (it.pa < 0) return;
     const int nn = wave_uniform(hdr[0]);
-    const int deg = wave_uniform(hdr[1]);
-    const int posoff = wave_uniform(hdr[2]);
     const int rkoff = wave_uniform(hdr[8]);
-    const int rl = DIM * deg;
+    const int rl = DIM * wave_uniform(hdr[1]);
     const bool hi = lane >= NG;
     const int node = lane & (NG - 1);
-    const uint16_t *n2l = sn2l + node;
-    const int pa = ldc(P.sig_pairs, 2 * posoff + 2 * r);
-    if (pa < 0) return;
-    const int pb = ldc(P.sig_pairs, 2 * posoff + 2 * r + 1);
-    const bool split = pb == pa;
-    const int c0 = ldc(P.sig_pos_ptr, posoff + pa);
-    const int na = ldc(P.sig_pos_ptr, posoff + pa + 1) - c0;
-    int lo0 = c0, nlo = na, hi0 = c0, nhi = 0;
-    if (split) {
-        nlo = (na + 1) / 2;
-        hi0 = c0 + nlo;
-        nhi = na - nlo;
-    } else if (pb >= 0) {
-        hi0 = ldc(P.sig_pos_ptr, posoff + pb);
-        nhi = ldc(P.sig_pos_ptr, posoff + pb + 1) - hi0;
-    }
-    if (!fin) {
-        const int mycnt = hi ? nhi : nlo;
-        const int32_t *lo_p = P.sig_contrib + lo0;
-        const int32_t *hi_p = P.sig_contrib + (nhi > 0 ? hi0 : lo0);
-        for (int t0 = 0; t0 < nlo; t0 += 8) {
-            const Codes8 cl = ld_codes8(lo_p + t0), ch = ld_codes8(hi_p + t0);
-#pragma unroll
-            for (int u = 0; u < 8; u++) {
-                if (t0 + u >= nlo) break;
-                const bool oku = t0 + u < mycnt;
-                const int code = oku ? (hi && nhi > 0 ? ch[u] : cl[u]) : 0;
-                const int k = code >> 16, i = (code >> 8) & 255, j = code & 255;
-                contribute_point<DIM, NEN, QP>(Gs, n2l[k * NG], i, j, oku, acc);
-            }
-        }
-        return;
-    }
-    if (split) {
+    if (it.split()) {
 #pragma unroll
         for (int a = 0; a < DIM; a++)
 #pragma unroll
             for (int c = 0; c < DIM; c++) acc[a][c] += __shfl_xor(acc[a][c], NG);
     }
-    const int pme = hi ? pb : pa;
-    if (node < nn && pme >= 0 && !(split && hi)) {
+    const int pme = hi ? it.pb : it.pa;
+    if (node < nn && pme >= 0 && !(it.split() && hi)) {
         const int pcsr = rkoff >= 0 ? (int)P.grp_rank[rkoff + pme * NG + node] : pme;
         double tr = 0.0;
 #pragma unroll
@@ -1308,8 +1376,9 @@ __device__ __forceinline__ void point_pairs(const AsmParams &P, const int *hdr, 
     }
 }
 
-// Wide item r (r < number of wide items): as point_pairs, the phases of a
-// position added by the butterfly at the end
+// Wide item r (r < number of wide items): a pass's terms, or with fin (after the
+// last pass) the phases of a position added by the butterfly and the lane's
+// block to its row block
 template <int DIM, int NEN, int QP>
 __device__ __forceinline__ void point_wide(const AsmParams &P, const int *hdr, int r, const double *Gs,
                                            const uint16_t *sn2l, int lane, double *stage, bool fin,
@@ -1351,7 +1420,8 @@ __device__ __forceinline__ void point_wide(const AsmParams &P, const int *hdr, i
             if (t >= nt) break;
             if (pk[t] >= 0) {
                 const int k = pk[t] >> 16, i = (pk[t] >> 8) & 255, j = pk[t] & 255;
-                contribute_point<DIM, NEN, QP>(Gs, n2l[k * NG], i, j, true, acc);
+                const int slot = n2l[k * NG];
+                contribute_entries<DIM, NEN, QP>(Gs, i * kGroupElems + slot, j * kGroupElems + slot, true, acc);
             }
         }
         return;
@@ -1389,9 +1459,15 @@ __device__ __forceinline__ void point_wide(const AsmParams &P, const int *hdr, i
 // sum: the passes in order; in a pass, the lane's contributions in the
 // plan's order, each over the pass's points in order; then a split
 // position's halves, or a wide item's phases, as in k_assemble.
-// Jittered 120x40x40 hexahedra: 225 us, against 241 with the gradients read 8
-// bytes at a time (six LDS reads per contribution and point instead of four)
-// and the items dealt w, w + NW.
+// Bound by its vector instructions, of which one in four was an FMA of a
+// contribution: what does not change from pass to pass (a pairs item's lists,
+// the LDS entries of its first contributions; two fewer for the second item,
+// whose lists are shorter, as 128 registers hold four waves per SIMD) is found
+// once, an entry gives its addresses by two shifts, and the geometry is read
+// at a base of the wave with a 32-bit offset.  Jittered 120x40x40 hexahedra:
+// 198 us, against 226 with all of that found anew in every pass, and 241 with
+// the gradients read 8 bytes at a time (six LDS reads per contribution and point
+// instead of four) and the items dealt w, w + NW.
 template <int DIM>
 struct PointShape {
     static constexpr int threads = DIM == 2 ? 256 : 512;
@@ -1400,7 +1476,7 @@ struct PointShape {
 };
 
 template <int DIM, int NEN>
-__global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(AsmParams P) {
+__global__ __launch_bounds__(PointShape<DIM>::threads, 4) void k_assemble_point(AsmParams P) {
     constexpr int kThreads = PointShape<DIM>::threads;
     constexpr int QP = PointShape<DIM>::qp;
     constexpr int NW = kThreads / 64;
@@ -1413,7 +1489,7 @@ __global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(Asm
     static_assert(kGroupElems <= kThreads, "one thread per slot");
     extern __shared__ __align__(16) unsigned char smem[];
     // the gradients and, after the last pass, the stage in the same bytes
-    double *sg = reinterpret_cast<double *>(smem);                  // [QP][NEN] gradients (point_at)
+    double *sg = reinterpret_cast<double *>(smem);                  // [QP][NEN] gradients (put_gradient)
     double *sE = sg + QP * NEN * DIM * kGroupElems;                 // [kGroupElems] sqrt(E(rho))
     int32_t *sid = reinterpret_cast<int32_t *>(sE + kGroupElems);  // [kGroupElems] column of qgeo
     double *stage = sg;                                             // [P.stage]
@@ -1462,8 +1538,7 @@ __global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(Asm
 #pragma unroll
             for (int c = 0; c < DIM; c++) acc[it][a][c] = 0.0;
     // item (point qq of the pass, slot): the slot's gradients at that point,
-    // sg[point_at(qq k, a, slot)] = g_k[a] = sqrt(E) sum_m grad phi_k(xi_q)[m]
-    // G'_q[m][a]
+    // g_k[a] = sqrt(E) sum_m grad phi_k(xi_q)[m] G'_q[m][a]
     auto gradients = [&](const double (&G)[D2], double se, int q, int qq, int slot) {
         double f[DIM][2];
 #pragma unroll
@@ -1492,8 +1567,7 @@ __global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(Asm
                 for (int m = 1; m < DIM; m++) g[a] = fma(r[m], G[m * DIM + a], g[a]);
                 g[a] = se * g[a];
             }
-            *reinterpret_cast<Two *>(sg + point_at<DIM>(qq * NEN + k, 0, slot)) = Two{g[0], g[1]};
-            if constexpr (DIM == 3) sg[point_at<DIM>(qq * NEN + k, 2, slot)] = g[2];
+            put_gradient<DIM, NEN, QP>(sg, (qq * NEN + k) * kGroupElems + slot, g);
         }
     };
     auto modulus_root = [&](int id) {
@@ -1507,20 +1581,43 @@ __global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(Asm
     const bool has = kOneItem && ne > 0 && tid < QP * ne;
     const int iqq = has ? tid / ne : 0, islot = has ? tid - iqq * ne : 0;
     int iid = 0;
-    double ise = 0.0, Gc[D2], Gn[D2];
+    double ise = 0.0, Gc[D2];
+    // entry c of pass pass: a base of the wave and the lane's 32-bit offset
+    // (fewer than 2^25 elements: assemble_point_fits)
+    uint32_t ioff = 0;
+    auto load_geo = [&](double (&G)[D2], int pass) {
+#pragma unroll
+        for (int c = 0; c < D2; c++) {
+            const char *b = reinterpret_cast<const char *>(P.qgeo + (int64_t)(pass * QP * D2 + c) * NC);
+            G[c] = *reinterpret_cast<const double *>(b + ioff);
+        }
+    };
     if (has) {
         iid = P.grp_elems[eoff + islot];
         ise = modulus_root(iid);
+        ioff = 8u * ((uint32_t)(iqq * D2) * (uint32_t)NC + (uint32_t)iid);
+        load_geo(Gc, 0);
+    }
+    // the wave's items: r = w and 2 NW - 1 - w
+    const int posoff = wave_uniform(ldc(P.sig_info, 4 * sgi + 2));
+    const int wi0 = wave_uniform(ldc(P.sig_witem_ptr, sgi));
+    const int nitems = wide ? wave_uniform(ldc(P.sig_witem_ptr, sgi + 1)) - wi0
+                            : wave_uniform(ldc(P.sig_info, 4 * sgi + 1)) + 1;
+    PairItem item[2];
+    int kept0[4], kept1[2];
 #pragma unroll
-        for (int c = 0; c < D2; c++) Gc[c] = P.qgeo[(int64_t)(iqq * D2 + c) * NC + iid];
+    for (int it = 0; it < 2; it++) {
+        const int r = it == 0 ? w : 2 * NW - 1 - w;
+        item[it].pa = -1;
+        item[it].pb = -2;
+        item[it].nlo = item[it].nhi = item[it].lo0 = item[it].hi0 = 0;
+        if (!wide && r < nitems) read_pair(P, posoff, r, item[it]);
     }
     for (int pass = 0; pass < NPASS; pass++) {
         if constexpr (kOneItem) {
             if (has) {
                 gradients(Gc, ise, pass * QP + iqq, iqq, islot);
-                if (pass + 1 < NPASS)
-#pragma unroll
-                    for (int c = 0; c < D2; c++) Gn[c] = P.qgeo[(int64_t)(((pass + 1) * QP + iqq) * D2 + c) * NC + iid];
+                if (pass + 1 < NPASS) load_geo(Gc, pass + 1);
             }
         } else {
             // several items per thread (2D: one pass)
@@ -1547,29 +1644,26 @@ __global__ __launch_bounds__(PointShape<DIM>::threads) void k_assemble_point(Asm
             }
         }
         __syncthreads();
-        const int nitems = wide ? wave_uniform(shdr[6]) : wave_uniform(shdr[1]) + 1;
 #pragma unroll
         for (int it = 0; it < 2; it++) {
             const int r = it == 0 ? w : 2 * NW - 1 - w;
-            if (r >= nitems) continue;
-            if (wide) point_wide<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, false, acc[it]);
-            else point_pairs<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, false, acc[it]);
+            if (!wide) {
+                if (item[it].nlo <= 0) continue;
+                if (it == 0) point_pairs<DIM, NEN, QP>(P, item[0], kept0, pass == 0, sg, sn2l, lane, acc[0]);
+                else point_pairs<DIM, NEN, QP>(P, item[1], kept1, pass == 0, sg, sn2l, lane, acc[1]);
+            } else if (r < nitems) {
+                point_wide<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, false, acc[it]);
+            }
         }
         __syncthreads();
-        if constexpr (kOneItem) {
-#pragma unroll
-            for (int c = 0; c < D2; c++) Gc[c] = Gn[c];
-        }
     }
     // the blocks into the stage (over the gradients, read by now), then the
     // group's rows out as in k_assemble
-    const int nitems = wide ? wave_uniform(shdr[6]) : wave_uniform(shdr[1]) + 1;
 #pragma unroll
     for (int it = 0; it < 2; it++) {
         const int r = it == 0 ? w : 2 * NW - 1 - w;
-        if (r >= nitems) continue;
-        if (wide) point_wide<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, true, acc[it]);
-        else point_pairs<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, true, acc[it]);
+        if (!wide) finish_pairs<DIM>(P, shdr, item[it], lane, stage, acc[it]);
+        else if (r < nitems) point_wide<DIM, NEN, QP>(P, shdr, r, sg, sn2l, lane, stage, true, acc[it]);
     }
     __syncthreads();
     store_rows<DIM, NW>(P, shdr, srows, stage, w, lane);
@@ -2486,8 +2580,10 @@ static size_t point_lds(int dim, int nen, int64_t stage, int kmax) {
     return std::max(grad, 8 * (size_t)stage) + kGroupNodes * 2 * 4 + 2 * (size_t)kmax * kGroupNodes;
 }
 
-bool assemble_point_fits(int elem, int64_t stage, int kmax, int max_items) {
+bool assemble_point_fits(int elem, int64_t n_cells, int64_t stage, int kmax, int max_items) {
     if (elem != SOPTX_QUAD4 && elem != SOPTX_HEX8) return false;
+    // the lane's byte offset into the geometry of a pass: 8 (9 n_cells + element)
+    if (n_cells >= (int64_t)1 << 25) return false;
     const int dim = elem == SOPTX_QUAD4 ? 2 : 3;
     const int items = dim == 2 ? PointShape<2>::items : PointShape<3>::items;
     return max_items <= items && point_lds(dim, 1 << dim, stage, kmax) + 64 <= 160 * 1024;

@@ -433,7 +433,7 @@ static int general_form(soptx_pattern h) {
     const int v = g_general_variant.load();
     if (h->n_row_groups > 0 && v != 0) return 3;
     if (!h->qgeo || v == 0) return 0;
-    if (v != 1 && assemble_point_fits(h->elem, h->stage, h->kmax, h->max_items)) return 1;
+    if (v != 1 && assemble_point_fits(h->elem, h->n_cells, h->stage, h->kmax, h->max_items)) return 1;
     if (assemble_quad_fits(h->elem, h->stage, h->kmax)) return 2;
     return 0;
 }
