@@ -219,6 +219,17 @@ __device__ __forceinline__ void accumulate_diag(const T (&dd)[DIM][DIM], const T
         }
 }
 
+// Entry (a, c) of lam A + mu A^T + mu tr(A) I, its roundings written out: left
+// to the compiler, which of the two products is rounded before the addition
+// changes with the code around it, and K's last bits with it.
+template <int DIM>
+__device__ __forceinline__ double block_entry(const double (&A)[DIM][DIM], int a, int c, double tr, double lam,
+                                              double mu) {
+    if (a == c) return fma(mu, tr, fma(lam, A[a][a], mu * A[a][a]));
+    if (a < c) return fma(mu, A[c][a], lam * A[a][c]);
+    return fma(lam, A[a][c], mu * A[c][a]);
+}
+
 static size_t assemble_lds_bytes(int dim, int nen, int prec, int64_t stage, int kmax) {
     const size_t csz = prec == kF64 ? 8 : 4;
     return 2 * 8 * (size_t)stage + 2 * csz * dim * dim * kGroupElems + csz * nen * nen * dim * dim +
@@ -424,8 +435,7 @@ __device__ __forceinline__ void assemble_wide(const AsmParams &P, const int *hdr
             for (int a = 0; a < DIM; a++)
 #pragma unroll
                 for (int c = 0; c < DIM; c++) {
-                    double o = P.lam * acc[a][c] + P.mu * acc[c][a];
-                    if (a == c) o += P.mu * tr;
+                    double o = block_entry<DIM>(acc, a, c, tr, P.lam, P.mu);
                     if (FUSE && bcoff >= 0) o = dirichlet_entry(bcb, a, c, o);
                     st[a * rl + DIM * pcsr + c] = o;
                 }
@@ -572,8 +582,7 @@ __device__ __forceinline__ void assemble_pairs(const AsmParams &P, const int *hd
             for (int a = 0; a < DIM; a++)
 #pragma unroll
                 for (int c = 0; c < DIM; c++) {
-                    double o = P.lam * acc[a][c] + P.mu * acc[c][a];
-                    if (a == c) o += P.mu * tr;
+                    double o = block_entry<DIM>(acc, a, c, tr, P.lam, P.mu);
                     if (FUSE && bcoff >= 0) o = dirichlet_entry(bcb, a, c, o);
                     st[a * rl + DIM * pcsr + c] = o;
                 }
