@@ -218,6 +218,21 @@ int soptx_assemble_backward(soptx_pattern h, const soptx_material *m, const void
                             const uint8_t *d_dirichlet, const double *d_Kbar, void *d_drho,
                             int32_t prec, void *stream);
 
+/* The same gradient with scratch memory of the call's own, on the assembly
+ * plan's node groups: every row of Kbar is read once (120x40x40 hexahedra
+ * about an eighth of soptx_assemble_backward's time, which is one launch on
+ * the caller's arrays alone and gathers Kbar element by element).  d_scratch:
+ * at least soptx_backward_scratch_size bytes of device memory, 8-byte aligned,
+ * contents of no matter; it must not be used by other work until the stream
+ * has passed the call (a call captured in a graph uses it in every replay).
+ * Where that size is 0 (2D meshes of up to 20,000 cells, handles of general
+ * elements) d_scratch is not looked at and soptx_assemble_backward runs.
+ * Each form sums in a fixed order of its own; they differ in rounding. */
+int soptx_backward_scratch_size(soptx_pattern h, int64_t *bytes);
+int soptx_assemble_backward_scratch(soptx_pattern h, const soptx_material *m, const void *d_rho,
+                                    const uint8_t *d_dirichlet, const double *d_Kbar, void *d_drho,
+                                    int32_t prec, void *d_scratch, int64_t scratch_bytes, void *stream);
+
 /* y = K x for K in the pattern's CSR (d_K_vals: [nnz] double), x and y
  * [ndof] double (the matrix-vector product of the equilibrium system
  * K u = f, Sec. 2.2).  Each row is summed in a fixed order.  Asynchronous on

@@ -90,6 +90,8 @@ def lib():
         "soptx_dirichlet_info": [_P, ctypes.POINTER(_I64), ctypes.POINTER(_I64)],
         "soptx_step": [_P, _P, ctypes.POINTER(Material), _P, _P, _P, _P, _P, _P, _I32, _P],
         "soptx_assemble_backward": [_P, ctypes.POINTER(Material), _P, _P, _P, _P, _I32, _P],
+        "soptx_backward_scratch_size": [_P, ctypes.POINTER(_I64)],
+        "soptx_assemble_backward_scratch": [_P, ctypes.POINTER(Material), _P, _P, _P, _P, _I32, _P, _I64, _P],
         "soptx_spmv": [_P, _P, _P, _P, _P],
         "soptx_pcg": [_P, _P, _P, _P, ctypes.c_double, _I32, ctypes.POINTER(_I32), ctypes.POINTER(ctypes.c_double),
                       _P],

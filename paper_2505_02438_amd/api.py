@@ -152,6 +152,9 @@ class Pattern:
         ndof, nnz = ctypes.c_int64(), ctypes.c_int64()
         check(lib().soptx_pattern_info(h, ctypes.byref(ndof), ctypes.byref(nnz), None, None), "pattern_info")
         self.ndof, self.nnz = ndof.value, nnz.value
+        scratch = ctypes.c_int64()
+        check(lib().soptx_backward_scratch_size(h, ctypes.byref(scratch)), "soptx_backward_scratch_size")
+        self._bwd_scratch = scratch.value
 
     @classmethod
     def from_mesh(cls, mesh, **kw) -> "Pattern":
@@ -334,18 +337,32 @@ class Pattern:
         return u, it.value, rel.value
 
     def backward(self, material: Material, rho, Kbar, mask=None, out=None, prec: int = FP64, stream=None):
-        """drho_e = E'(rho_e) <Kbar, K_e^0> over the element's slots (reverse of assemble)."""
+        """drho_e = E'(rho_e) <Kbar, K_e^0> over the element's slots (reverse of assemble).
+
+        The scratch is a tensor of the call's own, from torch's allocator on the
+        call's stream (during a capture by torch, from the graph's pool).  If
+        there is no memory for it, the form without scratch runs; its sums are
+        in another order."""
         import torch
         if out is None:
             with _on(stream):
                 out = torch.empty(self.n_cells, dtype=self._rho_dtype(prec), device=rho.device)
         mc = material._c()
-        check(lib().soptx_assemble_backward(self._h, ctypes.byref(mc),
-                                            _dptr(rho, "rho", self._rho_dtype(prec), self.n_cells),
-                                            _dptr(mask, "mask", torch.uint8, self.ndof),
-                                            _dptr(Kbar, "Kbar", torch.float64, self.nnz),
-                                            _dptr(out, "drho", self._rho_dtype(prec), self.n_cells), prec,
-                                            _stream_ptr(stream)), "soptx_assemble_backward")
+        args = (self._h, ctypes.byref(mc), _dptr(rho, "rho", self._rho_dtype(prec), self.n_cells),
+                _dptr(mask, "mask", torch.uint8, self.ndof), _dptr(Kbar, "Kbar", torch.float64, self.nnz),
+                _dptr(out, "drho", self._rho_dtype(prec), self.n_cells), prec)
+        scratch = None
+        if self._bwd_scratch:
+            try:
+                with _on(stream):
+                    scratch = torch.empty(self._bwd_scratch, dtype=torch.uint8, device=rho.device)
+            except torch.cuda.OutOfMemoryError:
+                pass
+        if scratch is None:
+            check(lib().soptx_assemble_backward(*args, _stream_ptr(stream)), "soptx_assemble_backward")
+        else:
+            check(lib().soptx_assemble_backward_scratch(*args, scratch.data_ptr(), self._bwd_scratch,
+                                                        _stream_ptr(stream)), "soptx_assemble_backward_scratch")
         return out
 
 

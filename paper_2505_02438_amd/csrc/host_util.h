@@ -13,19 +13,15 @@ namespace soptx {
 // Scratch of at least n doubles for work on (device, stream); `use` keeps
 // independent buffers apart: 0 = reduction partials of the energy kernel,
 // 1 = CG vectors, 2 = filter chain rule, 3 = OC bisection state and partials,
-// 4 = element matrices of the per-quadrature-point assembly,
-// 5 = parts of the assembly backward.  Work on one
-// stream is ordered, so
-// one buffer per (device, stream, use) is race-free.  Held until the process
+// 4 = element matrices of the per-quadrature-point assembly.  Work on one
+// stream is ordered, so one buffer per (device, stream, use) is race-free
+// among the calls of one host thread; calls of several threads on one stream,
+// and replays of a graph captured there beside other work on that stream, have
+// to be ordered by the caller.  Held until the process
 // ends; when a call needs more, a larger buffer replaces it and the old one is
 // kept (not freed), so that a HIP graph captured earlier on the stream, which
 // holds the old address, still replays on valid memory.
 int get_workspace(int device, hipStream_t st, size_t n, double **out, int use);
-
-// The same buffer where it is there already or can be allocated now; false
-// otherwise (the stream is being captured, or the device is full): for calls
-// that have a form without a workspace.
-bool have_workspace(int device, hipStream_t st, size_t n, double **out, int use);
 
 // Copy a host vector into a new device allocation recorded in `allocs` (freed
 // with its handle); *dst = nullptr for an empty vector.  *bytes, if given,

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -56,26 +57,6 @@ int get_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
     }
     *out = w.buf;
     return SOPTX_OK;
-}
-
-bool have_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
-    {
-        std::lock_guard<std::mutex> lk(g_ws_mu);
-        auto it = g_ws.find(std::make_tuple(device, st, use));
-        if (it != g_ws.end() && it->second.n >= n) {
-            *out = it->second.buf;
-            return true;
-        }
-    }
-    // memory cannot be allocated while the stream is being captured
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (get_workspace(device, st, n, out, use) == SOPTX_OK) return true;
-    (void)hipGetLastError();
-    return false;
 }
 
 }  // namespace soptx
@@ -807,44 +788,71 @@ int soptx_compliance(soptx_pattern h, const soptx_material *m, const void *d_rho
     return soptx_evaluate(h, m, d_rho, d_u, d_f, nullptr, d_c, prec, stream);
 }
 
+static int check_backward(soptx_pattern h, const soptx_material *m, const void *d_rho, const double *d_Kbar,
+                          const void *d_drho, int32_t prec) {
+    if (!h || !valid_prec(prec)) return SOPTX_E_INVALID_ARG;
+    if (!h->affine) return not_affine(h);
+    const int rc = check_material(m);
+    if (rc) return rc;
+    if (h->n_cells > 0 && (!d_rho || !d_Kbar || !d_drho)) return SOPTX_E_INVALID_ARG;
+    return SOPTX_OK;
+}
+
+// The scratch of the backward on the plan's node groups: the parts of each
+// element (one per local node) and a word of its fixed dofs.  0 where the
+// element-by-element kernel runs in any case: small 2D meshes, whose calls
+// cost their launches (two or three against one).  Without and with a mask,
+// 10,000 quadrilaterals 8.8 and 14.9 us against 11.8 and 14.9, 20,000
+// triangles 8.8 and 9.5 against 12.0 and 14.7; 25,000 renumbered
+// quadrilaterals 16.6 and 34.2 against 11.9 and 14.9, 100,000 triangles 11.0
+// and 15.7 against 13.1 and 15.9 (in 3D 2,000 hexahedra 101 against 14).
+static int64_t backward_scratch_doubles(soptx_pattern h) {
+    if (!h->affine || (h->dim == 2 && h->n_cells <= 20000)) return 0;
+    return h->n_cells * (h->nen + 1);
+}
+
 int soptx_assemble_backward(soptx_pattern h, const soptx_material *m, const void *d_rho,
                             const uint8_t *d_dirichlet, const double *d_Kbar, void *d_drho, int32_t prec,
                             void *stream) {
-    if (!h || !valid_prec(prec)) return SOPTX_E_INVALID_ARG;
-    if (!h->affine) return not_affine(h);
-    int rc = check_material(m);
+    const int rc = check_backward(h, m, d_rho, d_Kbar, d_drho, prec);
     if (rc) return rc;
-    if (h->n_cells > 0 && (!d_rho || !d_Kbar || !d_drho)) return SOPTX_E_INVALID_ARG;
     if (h->n_cells == 0) return SOPTX_OK;
     DeviceGuard dg(h->device);
     if (!dg.ok) return SOPTX_E_DEVICE;
-    // On the plan's node groups, with the parts of each element in the
-    // stream's workspace; the element-by-element kernel where that memory
-    // cannot be had (a first call while the stream is being captured, or a
-    // full device): it needs no workspace.  It also serves small 2D meshes,
-    // whose calls cost their launches (two or three against one): without and
-    // with a mask, 10,000 quadrilaterals 8.8 and 14.9 us against 11.8 and
-    // 14.9, 20,000 triangles 8.8 and 9.5 against 12.0 and 14.7; 25,000
-    // renumbered quadrilaterals 16.6 and 34.2 against 11.9 and 14.9, 100,000
-    // triangles 11.0 and 15.7 against 13.1 and 15.9 (in 3D 2,000 hexahedra
-    // 101 against 14).
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    double *part = nullptr;
-    const bool small = h->dim == 2 && h->n_cells <= 20000;
-    if (!small && have_workspace(h->device, st, (size_t)h->n_cells * (h->nen + 1), &part, 5)) {
-        BwdGroupParams B{};
-        if ((rc = asm_params(h, m, d_rho, nullptr, prec, st, B.A))) return rc;
-        B.Kbar = d_Kbar; B.mask = d_dirichlet; B.cells = h->cells; B.part = part;
-        B.fixed = reinterpret_cast<uint32_t *>(part + h->n_cells * h->nen); B.drho = d_drho;
-        if (launch_backward_group(h->elem, prec, B, h->ngroups, st) != hipSuccess) return SOPTX_E_DEVICE;
-        return SOPTX_OK;
-    }
     BwdParams P{};
     P.cells = h->cells; P.row_ptr = h->row_ptr; P.pos = h->pos; P.geo = h->geo; P.rho = d_rho;
     P.Kbar = d_Kbar; P.M = h->M; P.M32 = h->M32; P.drho = d_drho; P.mask = d_dirichlet;
     P.n_cells = h->n_cells; P.E0 = m->E0; P.Emin = m->Emin; P.p = m->p; P.ip = int_exponent(m->p);
     lame(h, m, &P.lam, &P.mu);
-    if (launch_backward(h->elem, prec, P, st) != hipSuccess) return SOPTX_E_DEVICE;
+    if (launch_backward(h->elem, prec, P, static_cast<hipStream_t>(stream)) != hipSuccess) return SOPTX_E_DEVICE;
+    return SOPTX_OK;
+}
+
+int soptx_backward_scratch_size(soptx_pattern h, int64_t *bytes) {
+    if (!h || !bytes) return SOPTX_E_INVALID_ARG;
+    *bytes = backward_scratch_doubles(h) * (int64_t)sizeof(double);
+    return SOPTX_OK;
+}
+
+int soptx_assemble_backward_scratch(soptx_pattern h, const soptx_material *m, const void *d_rho,
+                                    const uint8_t *d_dirichlet, const double *d_Kbar, void *d_drho, int32_t prec,
+                                    void *d_scratch, int64_t scratch_bytes, void *stream) {
+    int rc = check_backward(h, m, d_rho, d_Kbar, d_drho, prec);
+    if (rc) return rc;
+    const int64_t need = backward_scratch_doubles(h);
+    if (need == 0) return soptx_assemble_backward(h, m, d_rho, d_dirichlet, d_Kbar, d_drho, prec, stream);
+    if (!d_scratch || reinterpret_cast<uintptr_t>(d_scratch) % sizeof(double) ||
+        scratch_bytes < need * (int64_t)sizeof(double))
+        return SOPTX_E_INVALID_ARG;
+    DeviceGuard dg(h->device);
+    if (!dg.ok) return SOPTX_E_DEVICE;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    double *part = static_cast<double *>(d_scratch);
+    BwdGroupParams B{};
+    if ((rc = asm_params(h, m, d_rho, nullptr, prec, st, B.A))) return rc;
+    B.Kbar = d_Kbar; B.mask = d_dirichlet; B.cells = h->cells; B.part = part;
+    B.fixed = reinterpret_cast<uint32_t *>(part + h->n_cells * h->nen); B.drho = d_drho;
+    if (launch_backward_group(h->elem, prec, B, h->ngroups, st) != hipSuccess) return SOPTX_E_DEVICE;
     return SOPTX_OK;
 }
 

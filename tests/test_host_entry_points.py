@@ -1,0 +1,12 @@
+"""Null arguments of the calls that need no device to be refused."""
+import ctypes
+
+from paper_2505_02438_amd import _lib
+
+
+def test_backward_scratch_refuses_null():
+    L = _lib.lib()
+    n = ctypes.c_int64(-7)
+    mat = _lib.Material(1.0, 1e-9, 0.3, 3.0, 0)
+    assert L.soptx_backward_scratch_size(None, ctypes.byref(n)) == -1 and n.value == -7
+    assert L.soptx_assemble_backward_scratch(None, ctypes.byref(mat), None, None, None, None, 0, None, 0, None) == -1
