@@ -7,6 +7,7 @@
 
 #include <cmath>
 
+#include "../../include/soptx_debug.h"
 #include "../../include/soptx_oc.h"
 #include "host_util.h"
 #include "internal.h"
@@ -17,6 +18,13 @@ using namespace soptx;
 namespace {
 constexpr int kPassesPerCheck = 4;
 constexpr double kDirectTol = 1e-5;
+thread_local int t_last_form = -1;  // soptx_debug_oc_form
+}
+
+extern "C" int soptx_debug_oc_form(int32_t *form) {
+    if (!form) return SOPTX_E_INVALID_ARG;
+    *form = t_last_form;
+    return SOPTX_OK;
 }
 
 extern "C" int soptx_oc_update(int64_t n, const double *d_rho, const double *d_dc, const double *d_dv,
@@ -28,6 +36,7 @@ extern "C" int soptx_oc_update(int64_t n, const double *d_rho, const double *d_d
         prm->max_steps < 1 || prm->max_steps > 1000)
         return SOPTX_E_INVALID_ARG;
     *out = soptx_oc_result{0.0, 0.0, 0.0, 0};
+    t_last_form = -1;
     if (n == 0) return SOPTX_OK;
     if (!d_rho || !d_dc || !d_dv || !d_rho_new || d_rho_new == d_rho || d_rho_new == d_dc || d_rho_new == d_dv)
         return SOPTX_E_INVALID_ARG;
@@ -62,6 +71,7 @@ extern "C" int soptx_oc_update(int64_t n, const double *d_rho, const double *d_d
         if (h[5] != 0.0) {
             for (int k = 0; k < kOcSlots; k++)  // all are 0, positive or NaN: a NaN stays
                 if (h[8 + k] > h[6] || std::isnan(h[8 + k])) h[6] = h[8 + k];
+            t_last_form = 1;
             return result();
         }
         if (launch_oc_init(state, prm->lmax, acc, st) != hipSuccess) return SOPTX_E_DEVICE;
@@ -78,5 +88,6 @@ extern "C" int soptx_oc_update(int64_t n, const double *d_rho, const double *d_d
     if (launch_oc_apply(d_rho, d_dc, d_dv, n, prm->move, prm->eta, state, d_rho_new, part, st) != hipSuccess)
         return SOPTX_E_DEVICE;
     if (!read_state()) return SOPTX_E_DEVICE;
+    t_last_form = 0;
     return result();
 }

@@ -10,3 +10,10 @@ def test_backward_scratch_refuses_null():
     mat = _lib.Material(1.0, 1e-9, 0.3, 3.0, 0)
     assert L.soptx_backward_scratch_size(None, ctypes.byref(n)) == -1 and n.value == -7
     assert L.soptx_assemble_backward_scratch(None, ctypes.byref(mat), None, None, None, None, 0, None, 0, None) == -1
+
+
+def test_oc_form_before_any_update():
+    L = _lib.lib()
+    f = ctypes.c_int32(-7)
+    assert L.soptx_debug_oc_form(None) == -1
+    assert L.soptx_debug_oc_form(ctypes.byref(f)) == 0 and f.value == -1
