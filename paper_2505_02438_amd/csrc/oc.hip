@@ -209,7 +209,9 @@ __global__ __launch_bounds__(256) void k_oc_change(const double *__restrict__ pa
 // at the path's last l1 and vol <= V* at its last l2, each midpoint that went
 // up lies at or below that l1, each that went down at or above that l2, and
 // the loop would have decided the same.  (vol at the path's first l1 has to be
-// > V* as well: at a smaller lambda an overflow could still make a NaN.)
+// > V* as well: at a smaller lambda an overflow could still make a NaN.)  The
+// one term that can rise with lambda, dv < 0 with rho < 0 and eta 1 (with eta
+// 0.5 it is the root of a negative number), is a NaN in the proof, which fails.
 //
 // k_oc_search finds the root first: rho_new ~ clamp(s_e t) with s_e = rho
 // sqrt(-dc / dv) and t = lambda^-1/2 (eta 1: rho (-dc) / dv and 1 / lambda)
@@ -425,6 +427,9 @@ __global__ __launch_bounds__(256) void k_oc_check(OcArgs A, const double *__rest
         }
 #pragma unroll
         for (int k = 0; k < kOcProof; k++) a[k] += v * oc_new(r, d, v, l[k], A.move, A.eta);
+        if (v < 0.0 && r < 0.0)
+#pragma unroll
+            for (int k = 0; k < kOcProof; k++) a[k] = __builtin_nan("");
     }
 #pragma unroll
     for (int k = 0; k < kOcProof; k++) {
