@@ -225,8 +225,9 @@ int soptx_assemble_backward(soptx_pattern h, const soptx_material *m, const void
  * at least soptx_backward_scratch_size bytes of device memory, 8-byte aligned,
  * contents of no matter; it must not be used by other work until the stream
  * has passed the call (a call captured in a graph uses it in every replay).
- * Where that size is 0 (2D meshes of up to 20,000 cells, handles of general
- * elements) d_scratch is not looked at and soptx_assemble_backward runs.
+ * Where that size is 0 (2D meshes up to a size given by the element and the
+ * numbering, handles of general elements) d_scratch is not looked at and
+ * soptx_assemble_backward runs.
  * Each form sums in a fixed order of its own; they differ in rounding. */
 int soptx_backward_scratch_size(soptx_pattern h, int64_t *bytes);
 int soptx_assemble_backward_scratch(soptx_pattern h, const soptx_material *m, const void *d_rho,

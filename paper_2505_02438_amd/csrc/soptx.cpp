@@ -800,14 +800,27 @@ static int check_backward(soptx_pattern h, const soptx_material *m, const void *
 
 // The scratch of the backward on the plan's node groups: the parts of each
 // element (one per local node) and a word of its fixed dofs.  0 where the
-// element-by-element kernel runs in any case: small 2D meshes, whose calls
-// cost their launches (two or three against one).  Without and with a mask,
-// 10,000 quadrilaterals 8.8 and 14.9 us against 11.8 and 14.9, 20,000
-// triangles 8.8 and 9.5 against 12.0 and 14.7; 25,000 renumbered
-// quadrilaterals 16.6 and 34.2 against 11.9 and 14.9, 100,000 triangles 11.0
-// and 15.7 against 13.1 and 15.9 (in 3D 2,000 hexahedra 101 against 14).
+// element-by-element kernel runs in any case: 2D meshes whose calls cost their
+// launches (two or three against one, and the group's chain of tables, rows
+// and sums), up to a size that depends on the element and on whether the
+// numbering keeps an element's rows near each other (a plan in the given
+// order).  Element kernel against node groups, us without and with a mask,
+// FP64:
+//   quadrilaterals, given order: 2,500 cells 8.5 / 8.5, 14.6 / 11.0;
+//     5,000 8.4 / 8.6, 14.5 / 11.3; 10,000 10.6 / 8.9, 16.5 / 11.3
+//   canonical order: 400 9.1 / 8.7, 15.1 / 11.0; 2,500 14.7 / 9.2, 23.7 / 12.0
+//   triangles, given order: 20,000 5.7 / 9.3, 9.1 / 12.0; 60,000 7.3 / 10.7,
+//     10.5 / 13.4; 100,000 11.6 / 13.4, 16.1 / 16.1; 115,000 13.7 / 13.6, 18.7 / 16.4
+//   canonical order: 5,000 7.3 / 9.7, 11.2 / 12.4; 7,200 10.1 / 9.7, 14.8 / 12.3
+// In 3D the groups are the faster form from one element on (31.5 / 7.4, 64.9 /
+// 9.9; 343 hexahedra 75 / 10, 137 / 12).
 static int64_t backward_scratch_doubles(soptx_pattern h) {
-    if (!h->affine || (h->dim == 2 && h->n_cells <= 20000)) return 0;
+    if (!h->affine) return 0;
+    const bool canonical = h->elem_by_rank != nullptr;
+    int64_t element_cells = 0;
+    if (h->elem == SOPTX_QUAD4) element_cells = canonical ? 400 : 5000;
+    if (h->elem == SOPTX_TRI3) element_cells = canonical ? 7000 : 100000;
+    if (h->n_cells <= element_cells) return 0;
     return h->n_cells * (h->nen + 1);
 }
 
