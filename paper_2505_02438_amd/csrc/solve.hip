@@ -317,8 +317,13 @@ __device__ __forceinline__ double lanes_sum(double x) {
 template <int DIM, int L>
 __global__ __launch_bounds__(256) void k_cg_step_spmv(CgStep A, int it, bool check) {
     __shared__ double red[1][256];
-    const bool stopped = A.fin[0] != 0.0;  // looked at before the first write: nothing waits for it alone
-    const bool first = it == 0;            // p = z
+    // Looked at before the first write: nothing waits for it alone.  In a launch
+    // that checks only block 0, which may write the stop, looks at it (all its
+    // waves before the barrier ahead of that write); the other blocks would find
+    // it or not by when they run, and work on, into buffers that nothing reads
+    // after a stop.
+    const bool stopped = (!check || blockIdx.x == 0) && A.fin[0] != 0.0;
+    const bool first = it == 0;  // p = z
     const double *__restrict__ z = A.z;
     const double *__restrict__ po = A.p[(it & 1) ^ 1];
     double *__restrict__ pn = A.p[it & 1];
