@@ -94,6 +94,12 @@ int soptx_debug_set_general_variant(int32_t v);
  * general tables. */
 int soptx_debug_general_path(soptx_pattern h, int32_t *form);
 
+/* Test hook: the iteration that soptx_pcg runs, process-wide: -1 (default) =
+ * two launches per iteration on small systems, five on others; 0 = five on
+ * every system.  Both give the same bits.  SOPTX_E_INVALID_ARG for other
+ * values. */
+int soptx_debug_set_pcg_variant(int32_t v);
+
 /* The form of the calling thread's last soptx_oc_update, in *form: 1 = the
  * path predicted and proved, 0 = the passes (no prediction for these
  * parameters, or no proof), -1 = none yet, or one that did no device work or

@@ -18,6 +18,8 @@ namespace {
 //
 // The equilibrium system K u = f of the compliance problem, solved by
 // conjugate gradients with a node-block Jacobi preconditioner on the assembled CSR values.
+// In the iteration every product that is added to a sum is an fma, written out:
+// the kernels of both its forms round alike, whatever the compiler would contract.
 //
 // y = K x.  K is a sum of DIM x DIM blocks, so a node's DIM rows share one
 // neighbour list: row DIM I + a holds, for neighbour J = nb(I)[q], the
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(256) void k_spmv(const int32_t *__restrict__ row_pt
 #pragma unroll
             for (int a = 0; a < DIM; a++)
 #pragma unroll
-                for (int e = 0; e < DIM; e++) acc[a] += K[b + a * rl + DIM * q + e] * xj[e];
+                for (int e = 0; e < DIM; e++) acc[a] = fma(K[b + a * rl + DIM * q + e], xj[e], acc[a]);
         }
     }
 #pragma unroll
@@ -62,7 +64,7 @@ __global__ __launch_bounds__(256) void k_spmv(const int32_t *__restrict__ row_pt
 #pragma unroll
         for (int a = 0; a < DIM; a++) {
             y[DIM * I + a] = acc[a];
-            xy += x[DIM * I + a] * acc[a];
+            xy = fma(x[DIM * I + a], acc[a], xy);
         }
     }
     if (!xy_part) return;
@@ -145,8 +147,8 @@ __device__ __forceinline__ void cg_node(int mode, double al, int64_t I, const do
     } else {
 #pragma unroll
         for (int a = 0; a < DIM; a++) {
-            u[d0 + a] += al * p[d0 + a];
-            ri[a] = r[d0 + a] - al * q[d0 + a];
+            u[d0 + a] = fma(al, p[d0 + a], u[d0 + a]);
+            ri[a] = fma(-al, q[d0 + a], r[d0 + a]);
         }
     }
     const double *bi = binv + (int64_t)DIM * DIM * I;
@@ -154,12 +156,12 @@ __device__ __forceinline__ void cg_node(int mode, double al, int64_t I, const do
     for (int a = 0; a < DIM; a++) {
         double t = 0.0;
 #pragma unroll
-        for (int c = 0; c < DIM; c++) t += bi[a * DIM + c] * ri[c];
+        for (int c = 0; c < DIM; c++) t = fma(bi[a * DIM + c], ri[c], t);
         r[d0 + a] = ri[a];
         z[d0 + a] = t;
         if (mode == 0) p[d0 + a] = t;
-        rz += ri[a] * t;
-        rr += ri[a] * ri[a];
+        rz = fma(ri[a], t, rz);
+        rr = fma(ri[a], ri[a], rr);
     }
 }
 
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(256) void k_cg_vec(int mode, const double *__restri
 __global__ __launch_bounds__(256) void k_cg_p(double *__restrict__ p, const double *__restrict__ z,
                                               const double *__restrict__ sc, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = z[i] + sc[2] * p[i];
+    if (i < n) p[i] = fma(sc[2], p[i], z[i]);
 }
 
 // ---- The iteration of small systems: two launches.

@@ -570,6 +570,15 @@ int soptx_spmv(soptx_pattern h, const double *d_K_vals, const double *d_x, doubl
     return SOPTX_OK;
 }
 
+// which iteration small systems run (soptx_debug_set_pcg_variant)
+static std::atomic<int> g_pcg_variant{-1};
+
+int soptx_debug_set_pcg_variant(int32_t v) {
+    if (v != -1 && v != 0) return SOPTX_E_INVALID_ARG;
+    g_pcg_variant = v;
+    return SOPTX_OK;
+}
+
 int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double *d_u, double rtol,
               int32_t max_iter, int32_t *h_iters, double *h_relres, void *stream) {
     if (!h || !h_iters || !h_relres || max_iter < 0 || !(rtol >= 0.0)) return SOPTX_E_INVALID_ARG;
@@ -588,7 +597,7 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
     // themselves: each of their blocks re-reads the other launch's partials,
     // which pays while that is a few MB (nbs * nbv doubles); both forms give the
     // same bits.
-    const bool small = nbs * nbv <= (int64_t)1 << 22;
+    const bool small = g_pcg_variant.load() != 0 && nbs * nbv <= (int64_t)1 << 22;
     // r, z, p, q, the node blocks of the preconditioner (DIM doubles per dof),
     // partials, 2 x 8 scalars, a stop record; small systems: a second p
     double *ws = nullptr;

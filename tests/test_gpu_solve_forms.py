@@ -1,6 +1,7 @@
 """The CG's two-launch form on systems of many blocks: a stop at a check while
 the launches enqueued ahead of its result still run, beside other solves, and
-the iterate it leaves (that of the same number of iterations, bit for bit)."""
+the iterate it leaves (that of the same number of iterations, bit for bit); and
+the same bits from the five launches of larger systems."""
 import ctypes
 import threading
 
@@ -47,3 +48,29 @@ def test_stops_beside_other_solves():
     [t.start() for t in th]
     [t.join() for t in th]
     assert len(stops) >= 1 and not bad
+
+
+def _separate(fn):
+    L = _lib.lib()
+    assert L.soptx_debug_set_pcg_variant(0) == 0
+    try:
+        return fn()
+    finally:
+        L.soptx_debug_set_pcg_variant(-1)
+
+
+# one block; a few; more than 1,024 and more than 4,096 blocks of partials of
+# the product (16 nodes each in 3D, 32 in 2D), where a thread's share of the sum
+# takes several rounds
+@pytest.mark.parametrize("elem,dims", [(I.QUAD4, (3, 2)), (I.QUAD4, (150, 50)), (I.QUAD4, (300, 260)),
+                                       (I.TRI3, (77, 31)), (I.HEX8, (2, 1, 1)), (I.HEX8, (14, 13, 11)),
+                                       (I.HEX8, (40, 30, 20)), (I.HEX8, (66, 40, 26)), (I.TET10, (5, 4, 3))])
+def test_two_launches_are_the_five(elem, dims):
+    """u, the iterations and the residual bit for bit, at a cap within and at
+    the end of a check's eight and at a stop."""
+    pat, K, f = _system(elem, dims)
+    for rtol, cap in ((0.0, 1), (0.0, 13), (0.0, 24), (1e-3, 400)):
+        u, it, rel = pat.pcg(K, f, rtol=rtol, max_iter=cap)
+        v, it5, rel5 = _separate(lambda: pat.pcg(K, f, rtol=rtol, max_iter=cap))
+        assert it == it5 and torch.equal(u, v)
+        assert rel == rel5 or (np.isnan(rel) and np.isnan(rel5))

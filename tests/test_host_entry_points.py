@@ -17,3 +17,8 @@ def test_oc_form_before_any_update():
     f = ctypes.c_int32(-7)
     assert L.soptx_debug_oc_form(None) == -1
     assert L.soptx_debug_oc_form(ctypes.byref(f)) == 0 and f.value == -1
+
+
+def test_pcg_variant_takes_its_values_only():
+    L = _lib.lib()
+    assert [L.soptx_debug_set_pcg_variant(v) for v in (0, 1, -2, -1)] == [0, -1, -1, 0]
