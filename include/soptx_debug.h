@@ -100,6 +100,13 @@ int soptx_debug_general_path(soptx_pattern h, int32_t *form);
  * values. */
 int soptx_debug_set_pcg_variant(int32_t v);
 
+/* Test hook: of the allocations that a call has another form without, the
+ * next `skip` go on as they would and the n after those fail, process-wide:
+ * soptx_pcg's second direction vector, then its stop record (without either:
+ * five launches per iteration).  n = 0 turns it off.  SOPTX_E_INVALID_ARG for
+ * negative values. */
+int soptx_debug_fail_optional(int32_t skip, int32_t n);
+
 /* The form of the calling thread's last soptx_oc_update, in *form: 1 = the
  * path predicted and proved, 0 = the passes (no prediction for these
  * parameters, or no proof), -1 = none yet, or one that did no device work or

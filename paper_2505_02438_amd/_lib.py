@@ -106,6 +106,7 @@ def lib():
         "soptx_debug_set_assembly_variant": [_I32],
         "soptx_debug_set_general_variant": [_I32],
         "soptx_debug_general_path": [_P, ctypes.POINTER(_I32)],
+        "soptx_debug_fail_optional": [_I32, _I32],
         "soptx_debug_set_pcg_variant": [_I32],
         "soptx_debug_oc_form": [ctypes.POINTER(_I32)],
         "soptx_debug_filter_matrix": [ctypes.POINTER(Mesh), ctypes.c_double, ctypes.POINTER(_I64),

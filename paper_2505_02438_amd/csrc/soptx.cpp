@@ -40,22 +40,24 @@ std::vector<double *> g_ws_retired;
 
 int get_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
     std::lock_guard<std::mutex> lk(g_ws_mu);
-    Workspace &w = g_ws[std::make_tuple(device, st, use)];
-    if (w.n < n) {
-        if (w.buf) {
-            try {
-                g_ws_retired.push_back(w.buf);
-            } catch (...) {
+    try {
+        Workspace &w = g_ws[std::make_tuple(device, st, use)];
+        if (w.n < n) {
+            g_ws_retired.reserve(g_ws_retired.size() + 1);
+            const size_t cap = n < 4096 ? 4096 : n;
+            double *p = nullptr;
+            if (hipMalloc(&p, cap * sizeof(double)) != hipSuccess) {
+                (void)hipGetLastError();  // not for the next launch to report
                 return SOPTX_E_OOM;
             }
-            w.buf = nullptr;
-            w.n = 0;
+            if (w.buf) g_ws_retired.push_back(w.buf);
+            w.buf = p;
+            w.n = cap;
         }
-        size_t cap = n < 4096 ? 4096 : n;
-        if (hipMalloc(&w.buf, cap * sizeof(double)) != hipSuccess) return SOPTX_E_OOM;
-        w.n = cap;
+        *out = w.buf;
+    } catch (...) {
+        return SOPTX_E_OOM;
     }
-    *out = w.buf;
     return SOPTX_OK;
 }
 
@@ -63,28 +65,53 @@ int get_workspace(int device, hipStream_t st, size_t n, double **out, int use) {
 
 
 namespace {
+// soptx_debug_fail_optional: how many allocations that a call can do without
+// still succeed, and how many then fail
+std::mutex g_fail_mu;
+int g_fail_skip = 0, g_fail_count = 0;
+bool fail_optional() {
+    std::lock_guard<std::mutex> lk(g_fail_mu);
+    if (g_fail_count == 0) return false;
+    if (g_fail_skip > 0) {
+        g_fail_skip--;
+        return false;
+    }
+    g_fail_count--;
+    return true;
+}
+
 // A record in host memory that kernels write (a stop of the CG), with an event;
-// a small pool per device, given back after each call.
+// up to kKept of them are kept between calls, each for its device.  Coherent
+// memory: the host reads what a kernel wrote once an event behind that kernel
+// has passed.  host is null where none could be had.
 struct StopRecord {
     double *host = nullptr, *dev = nullptr;
     hipEvent_t event = nullptr;
     int device;
     hipStream_t stream;
     StopRecord(int d, hipStream_t st) : device(d), stream(st) {
+        if (fail_optional()) return;
         {
             std::lock_guard<std::mutex> lk(mu());
-            auto &free = pool()[device];
-            if (!free.empty()) {
-                std::tie(host, dev, event) = free.back();
-                free.pop_back();
-            }
+            for (Kept &k : kept())
+                if (k.host && k.device == device) {
+                    host = k.host;
+                    dev = k.dev;
+                    event = k.event;
+                    k.host = nullptr;
+                    break;
+                }
         }
         if (!host) {
             void *p = nullptr, *q = nullptr;
-            if (hipHostMalloc(&p, 64, hipHostMallocMapped) != hipSuccess) return;
+            if (hipHostMalloc(&p, 64, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+                (void)hipGetLastError();
+                return;
+            }
             if (hipHostGetDevicePointer(&q, p, 0) != hipSuccess ||
                 hipEventCreateWithFlags(&event, hipEventDisableTiming) != hipSuccess) {
                 (void)hipHostFree(p);
+                (void)hipGetLastError();
                 return;
             }
             host = static_cast<double *>(p);
@@ -96,11 +123,13 @@ struct StopRecord {
         if (!host) return;
         // kernels of a call that failed may still write the record: they end first
         (void)hipStreamSynchronize(stream);
-        std::lock_guard<std::mutex> lk(mu());
-        auto &free = pool()[device];
-        if (free.size() < 16) {
-            free.emplace_back(host, dev, event);
-            return;
+        {
+            std::lock_guard<std::mutex> lk(mu());
+            for (Kept &k : kept())
+                if (!k.host) {
+                    k = Kept{host, dev, event, device};
+                    return;
+                }
         }
         (void)hipEventDestroy(event);
         (void)hipHostFree(host);
@@ -109,11 +138,19 @@ struct StopRecord {
     StopRecord &operator=(const StopRecord &) = delete;
 
 private:
-    using Slot = std::tuple<double *, double *, hipEvent_t>;
-    static std::mutex &mu() { static std::mutex m; return m; }
-    static std::map<int, std::vector<Slot>> &pool() {
-        static std::map<int, std::vector<Slot>> *p = new std::map<int, std::vector<Slot>>();
-        return *p;
+    struct Kept {
+        double *host, *dev;
+        hipEvent_t event;
+        int device;
+    };
+    static constexpr int kKept = 32;
+    static std::mutex &mu() {
+        static std::mutex m;
+        return m;
+    }
+    static Kept (&kept())[kKept] {
+        static Kept k[kKept] = {};
+        return k;
     }
 };
 }  // namespace
@@ -573,6 +610,14 @@ int soptx_spmv(soptx_pattern h, const double *d_K_vals, const double *d_x, doubl
 // which iteration small systems run (soptx_debug_set_pcg_variant)
 static std::atomic<int> g_pcg_variant{-1};
 
+int soptx_debug_fail_optional(int32_t skip, int32_t n) {
+    if (skip < 0 || n < 0) return SOPTX_E_INVALID_ARG;
+    std::lock_guard<std::mutex> lk(g_fail_mu);
+    g_fail_skip = skip;
+    g_fail_count = n;
+    return SOPTX_OK;
+}
+
 int soptx_debug_set_pcg_variant(int32_t v) {
     if (v != -1 && v != 0) return SOPTX_E_INVALID_ARG;
     g_pcg_variant = v;
@@ -597,14 +642,15 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
     // themselves: each of their blocks re-reads the other launch's partials,
     // which pays while that is a few MB (nbs * nbv doubles); both forms give the
     // same bits.
-    const bool small = g_pcg_variant.load() != 0 && nbs * nbv <= (int64_t)1 << 22;
+    bool small = g_pcg_variant.load() != 0 && nbs * nbv <= (int64_t)1 << 22;
     // r, z, p, q, the node blocks of the preconditioner (DIM doubles per dof),
-    // partials, 2 x 8 scalars, a stop record; small systems: a second p
+    // partials, 2 x 8 scalars, a stop record; small systems: a second p (where
+    // there is memory for it)
+    const size_t base = (4 + (size_t)h->dim) * (size_t)n + (size_t)npart + 2 * (size_t)nbv + 20;
     double *ws = nullptr;
-    int rc = get_workspace(h->device, st, (4 + (size_t)h->dim + (small ? 1 : 0)) * (size_t)n + (size_t)npart +
-                                               2 * (size_t)nbv + 20,
-                           &ws, 1);
-    if (rc) return rc;
+    if (small) small = !fail_optional() && get_workspace(h->device, st, base + (size_t)n, &ws, 1) == SOPTX_OK;
+    int rc = SOPTX_OK;
+    if (!small && (rc = get_workspace(h->device, st, base, &ws, 1))) return rc;
     double *r = ws, *z = r + n, *p = z + n, *q = p + n, *binv = q + n, *part = binv + h->dim * n,
            *part2 = part + npart, *sc = part2 + 2 * nbv, *fin = sc + 16, *p2 = fin + 4;
     double hs[8];
@@ -635,9 +681,8 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
     constexpr int kCheck = 8;
     int it = 0;
     double rel = 1.0;
-    if (small && max_iter > 0) {
-        StopRecord rec(h->device, st);
-        if (!rec.host) return SOPTX_E_OOM;
+    // two launches per iteration
+    auto pcg_small = [&](StopRecord &rec) -> int {
         CgStep A{};
         A.row_ptr = h->row_ptr; A.nb = h->nb; A.K = d_K_vals; A.binv = binv;
         A.u = d_u; A.r = r; A.z = z; A.q = q; A.p[0] = p; A.p[1] = p2;
@@ -668,6 +713,10 @@ int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double
         *h_iters = (int32_t)rec.host[1];
         *h_relres = std::sqrt(rec.host[2] / ref);
         return SOPTX_OK;
+    };
+    if (small && max_iter > 0) {
+        StopRecord rec(h->device, st);
+        if (rec.host) return pcg_small(rec);
     }
     while (it < max_iter) {
         if (launch_spmv(h->dim, h->row_ptr, h->nb, d_K_vals, p, q, part, h->n_nodes, st) != hipSuccess ||

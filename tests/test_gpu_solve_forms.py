@@ -74,3 +74,18 @@ def test_two_launches_are_the_five(elem, dims):
         v, it5, rel5 = _separate(lambda: pat.pcg(K, f, rtol=rtol, max_iter=cap))
         assert it == it5 and torch.equal(u, v)
         assert rel == rel5 or (np.isnan(rel) and np.isnan(rel5))
+
+
+@pytest.mark.parametrize("skip", [0, 1])
+def test_without_memory_for_the_two_launches(skip):
+    """No second direction vector, or no stop record: the five launches run."""
+    pat, K, f = _system(I.HEX8, (9, 8, 7))
+    want = pat.pcg(K, f, rtol=1e-6)
+    L = _lib.lib()
+    assert L.soptx_debug_fail_optional(skip, 1) == 0
+    try:
+        got = pat.pcg(K, f, rtol=1e-6)
+    finally:
+        L.soptx_debug_fail_optional(0, 0)
+    assert got[1:] == want[1:] and torch.equal(got[0], want[0])
+    assert pat.pcg(K, f, rtol=1e-6)[1:] == want[1:]

@@ -22,3 +22,8 @@ def test_oc_form_before_any_update():
 def test_pcg_variant_takes_its_values_only():
     L = _lib.lib()
     assert [L.soptx_debug_set_pcg_variant(v) for v in (0, 1, -2, -1)] == [0, -1, -1, 0]
+
+
+def test_fail_optional_refuses_negative_counts():
+    L = _lib.lib()
+    assert [L.soptx_debug_fail_optional(a, b) for a, b in ((-1, 0), (0, -1), (0, 0))] == [-1, -1, 0]
