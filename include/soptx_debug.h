@@ -103,7 +103,8 @@ int soptx_debug_set_pcg_variant(int32_t v);
 /* Test hook: of the allocations that a call has another form without, the
  * next `skip` go on as they would and the n after those fail, process-wide:
  * soptx_pcg's second direction vector, then its stop record (without either:
- * five launches per iteration).  n = 0 turns it off.  SOPTX_E_INVALID_ARG for
+ * five launches per iteration); the first and the last of a Q2 mesh's row
+ * group tables (element matrices).  n = 0 turns it off.  SOPTX_E_INVALID_ARG for
  * negative values. */
 int soptx_debug_fail_optional(int32_t skip, int32_t n);
 

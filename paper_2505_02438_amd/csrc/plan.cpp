@@ -762,8 +762,18 @@ int build_host_plan(const soptx_mesh *mesh, HostPlan &hp, bool general) {
                 }
         }))
             return SOPTX_E_OOM;
-        if ((rc = row_groups(mesh, n2e_ptr, n2e_e, hp))) return rc;
-        return general_table(mesh, hp);
+        if ((rc = general_table(mesh, hp))) return rc;
+        // the row groups are one form of the assembly: without host memory for
+        // their tables the mesh keeps the other
+        try {
+            rc = row_groups(mesh, n2e_ptr, n2e_e, hp);
+        } catch (const std::bad_alloc &) {
+            rc = SOPTX_E_OOM;
+        }
+        if (rc != SOPTX_E_OOM) return rc;
+        for (auto *v : {&hp.rg_info, &hp.rg_rows, &hp.rg_vis, &hp.rg_pairs, &hp.rg_ext}) v->clear();
+        hp.rg_code.clear();
+        return SOPTX_OK;
     }
 
     // ---- backward position table: position of cells[e][j] in the CSR

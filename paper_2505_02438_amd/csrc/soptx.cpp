@@ -283,6 +283,42 @@ int soptx_reference_tensor(int32_t elem, int32_t ref_method, double *M_out) {
     return reference_tensor(elem, ref_method, M_out);
 }
 
+// The row groups' tables and geometry of a Q2 mesh.  SOPTX_E_OOM: the device
+// has no room beside the pattern; nothing of them is held, and the assembly
+// forms element matrices.
+static int row_group_tables(soptx_pattern_s *h, const HostPlan &hp, hipStream_t st) {
+    const size_t held = h->allocs.size();
+    const int64_t bytes0 = h->stats.device_bytes;
+    const size_t bytes = (size_t)hp.n_cells * 27 * 10 * sizeof(double);
+    void *geo = nullptr;
+    int rc = fail_optional() ? SOPTX_E_OOM : SOPTX_OK;
+    if (!rc) {
+        h->allocs.reserve(held + 7);
+        if (hipMalloc(&geo, bytes) != hipSuccess) rc = SOPTX_E_OOM;
+        else h->allocs.push_back(geo);
+    }
+    if (!rc) rc = upload(h, hp.rg_info, &h->rg_info, st);
+    if (!rc) rc = upload(h, hp.rg_rows, &h->rg_rows, st);
+    if (!rc) rc = upload(h, hp.rg_vis, &h->rg_vis, st);
+    if (!rc) rc = upload(h, hp.rg_pairs, &h->rg_pairs, st);
+    if (!rc) rc = upload(h, hp.rg_ext, &h->rg_ext, st);
+    if (!rc) rc = fail_optional() ? SOPTX_E_OOM : upload(h, hp.rg_code, &h->rg_code, st);
+    if (rc == SOPTX_E_OOM) {
+        (void)hipGetLastError();  // not for the next launch to report
+        for (size_t k = held; k < h->allocs.size(); k++) (void)hipFree(h->allocs[k]);
+        h->allocs.resize(held);
+        h->stats.device_bytes = bytes0;
+        h->rg_info = h->rg_rows = h->rg_vis = h->rg_pairs = h->rg_ext = nullptr;
+        h->rg_code = nullptr;
+    }
+    if (rc) return rc;
+    h->stats.device_bytes += (int64_t)bytes;
+    h->geo27 = static_cast<double *>(geo);
+    if (launch_hex27_geometry(h->cells, h->coords, hp.n_cells, h->geo27, st) != hipSuccess) return SOPTX_E_DEVICE;
+    h->n_row_groups = (int64_t)hp.rg_info.size() / 4;
+    return SOPTX_OK;
+}
+
 static int build_pattern(const soptx_mesh *mesh, int32_t ref_method, bool general, soptx_pattern *out,
                          void *stream) {
     if (!out) return SOPTX_E_INVALID_ARG;
@@ -389,24 +425,9 @@ static int build_pattern(const soptx_mesh *mesh, int32_t ref_method, bool genera
                 return rc;
             }
         }
-        if (!hp.rg_info.empty()) {
-            if ((rc = upload(h, hp.rg_info, &h->rg_info, st)) || (rc = upload(h, hp.rg_rows, &h->rg_rows, st)) ||
-                (rc = upload(h, hp.rg_vis, &h->rg_vis, st)) || (rc = upload(h, hp.rg_pairs, &h->rg_pairs, st)) ||
-                (rc = upload(h, hp.rg_code, &h->rg_code, st)) || (rc = upload(h, hp.rg_ext, &h->rg_ext, st))) {
-                free_handle(h);
-                return rc;
-            }
-            void *p = nullptr;
-            const size_t bytes = (size_t)hp.n_cells * 27 * 10 * sizeof(double);
-            if (hipMalloc(&p, bytes) != hipSuccess) { free_handle(h); return SOPTX_E_OOM; }
-            h->allocs.push_back(p);
-            h->stats.device_bytes += (int64_t)bytes;
-            h->geo27 = static_cast<double *>(p);
-            if (launch_hex27_geometry(h->cells, h->coords, hp.n_cells, h->geo27, st) != hipSuccess) {
-                free_handle(h);
-                return SOPTX_E_DEVICE;
-            }
-            h->n_row_groups = (int64_t)hp.rg_info.size() / 4;
+        if (!hp.rg_info.empty() && (rc = row_group_tables(h, hp, st)) && rc != SOPTX_E_OOM) {
+            free_handle(h);
+            return rc;
         }
         if (hipStreamSynchronize(st) != hipSuccess) { free_handle(h); return SOPTX_E_DEVICE; }
         const int64_t ncontrib = hp.n_cells * (int64_t)nen * nen;
