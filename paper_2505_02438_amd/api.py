@@ -344,20 +344,20 @@ class Pattern:
         there is no memory for it, the form without scratch runs; its sums are
         in another order."""
         import torch
-        if out is None:
-            with _on(stream):
-                out = torch.empty(self.n_cells, dtype=self._rho_dtype(prec), device=rho.device)
-        mc = material._c()
-        args = (self._h, ctypes.byref(mc), _dptr(rho, "rho", self._rho_dtype(prec), self.n_cells),
-                _dptr(mask, "mask", torch.uint8, self.ndof), _dptr(Kbar, "Kbar", torch.float64, self.nnz),
-                _dptr(out, "drho", self._rho_dtype(prec), self.n_cells), prec)
+        dtype = self._rho_dtype(prec)
+        d_rho = _dptr(rho, "rho", dtype, self.n_cells)
         scratch = None
-        if self._bwd_scratch:
-            try:
-                with _on(stream):
-                    scratch = torch.empty(self._bwd_scratch, dtype=torch.uint8, device=rho.device)
-            except torch.cuda.OutOfMemoryError:
-                pass
+        with _on(stream):
+            if out is None:
+                out = torch.empty(self.n_cells, dtype=dtype, device=rho.device)
+            if self._bwd_scratch and d_rho is not None:
+                try:
+                    scratch = rho.new_empty(self._bwd_scratch // rho.element_size())
+                except torch.cuda.OutOfMemoryError:
+                    pass
+        mc = material._c()
+        args = (self._h, ctypes.byref(mc), d_rho, _dptr(mask, "mask", torch.uint8, self.ndof),
+                _dptr(Kbar, "Kbar", torch.float64, self.nnz), _dptr(out, "drho", dtype, self.n_cells), prec)
         if scratch is None:
             check(lib().soptx_assemble_backward(*args, _stream_ptr(stream)), "soptx_assemble_backward")
         else:

@@ -133,15 +133,17 @@ def test_scratch_arguments():
 
 def test_without_memory_for_the_scratch(monkeypatch):
     pr, pat, rho, mask, bars, _ = _setup(1, (6, 5, 7))
-    empty = torch.empty
-
     def full(*a, **kw):
-        if kw.get("dtype") == torch.uint8:
-            raise torch.cuda.OutOfMemoryError("full")
-        return empty(*a, **kw)
-    monkeypatch.setattr(torch, "empty", full)
+        raise torch.cuda.OutOfMemoryError("full")
+    monkeypatch.setattr(torch.Tensor, "new_empty", full)
     got = host(pat.backward(MAT, rho, bars[0], mask))
     monkeypatch.undo()
+    plain = torch.empty_like(rho)
+    mc = MAT._c()
+    assert _lib.lib().soptx_assemble_backward(pat._h, ctypes.byref(mc), rho.data_ptr(), mask.data_ptr(),
+                                              bars[0].data_ptr(), plain.data_ptr(), api.FP64,
+                                              torch.cuda.current_stream().cuda_stream) == 0
+    assert np.array_equal(got, host(plain))
     m = pr.mesh
     rp, ci = pat.pattern()
     Kb = host(bars[0]).copy()
