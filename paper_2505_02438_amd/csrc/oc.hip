@@ -88,8 +88,8 @@ __device__ __forceinline__ double wave_sum(double x) {
 }
 
 // part[node * gridDim.x + block] = sum over the block's elements of dv rho_new(lambda_node):
-// per thread in element order, then each wave by a butterfly, then the 4
-// waves in order
+// per thread in element order (by fma, as k_oc_check adds them: its volumes are
+// these, bit for bit), then each wave by a butterfly, then the 4 waves in order
 __global__ __launch_bounds__(256) void k_oc_eval(OcArgs A, const double *__restrict__ st, double *__restrict__ part) {
     __shared__ double red[4][kOcNodes];
     if (st[5] != 0.0) return;  // uniform: the bisection has ended
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(256) void k_oc_eval(OcArgs A, const double *__restr
     for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < A.n; e += (int64_t)gridDim.x * 256) {
         const double r = A.rho[e], d = A.dc[e], v = A.dv[e];
 #pragma unroll
-        for (int k = 0; k < kOcNodes; k++) acc[k] += v * oc_new(r, d, v, lam[k], A.move, A.eta);
+        for (int k = 0; k < kOcNodes; k++) acc[k] = fma(v, oc_new(r, d, v, lam[k], A.move, A.eta), acc[k]);
     }
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(256) void k_oc_check(OcArgs A, const double *__rest
             v = A.dv[e];
         }
 #pragma unroll
-        for (int k = 0; k < kOcProof; k++) a[k] += v * oc_new(r, d, v, l[k], A.move, A.eta);
+        for (int k = 0; k < kOcProof; k++) a[k] = fma(v, oc_new(r, d, v, l[k], A.move, A.eta), a[k]);
         if (v < 0.0 && r < 0.0)
 #pragma unroll
             for (int k = 0; k < kOcProof; k++) a[k] = __builtin_nan("");
