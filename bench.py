@@ -335,11 +335,14 @@ def hex27_run(stream, reps=10):
     the curved 60 x 20 x 20 cantilever (cubes of side 2 over the 120 x 40 x 40
     box, the Q1 cantilever's node lattice; interior nodes jittered by 0.15,
     seed 1005), rho ~ Beta(2, 2), FP64, Dirichlet rows; HIP events on the
-    bench stream.  Byte model of the assembly: element matrices written and
-    read back (n_cells 27^2 9 doubles each way), K written, the contribution
-    table (gptr, gent, gnode) read."""
+    bench stream.  Byte model of the assembly: by row groups (the form of this
+    mesh), K written and the per-point geometry (27 x 10 doubles per element)
+    read once, the groups' tables not counted; by element matrices, these
+    written and read back (n_cells 27^2 9 doubles each way), K written, the
+    contribution table (gptr, gent, gnode) read."""
+    import ctypes
     import torch
-    from paper_2505_02438_amd import api
+    from paper_2505_02438_amd import _lib, api
     from paper_2505_02438_amd import inputs as I
     pr = I.cantilever_hex27()
     m = pr.mesh
@@ -368,12 +371,18 @@ def hex27_run(stream, reps=10):
     dc = torch.empty(m.n_cells, dtype=torch.float64, device="cuda")
     c = torch.zeros(2, dtype=torch.float64, device="cuda")
     ev_avg = timed(lambda: pat.evaluate_general(mat, rho, u, dc=dc, c=c, stream=stream))
-    ke_bytes = m.n_cells * 27 * 27 * 9 * 8
-    nblk = pat.nnz // 9
-    table_bytes = 4 * (nblk + 1) + 4 * m.n_cells * 27 * 27 + 4 * nblk
-    moved = 2 * ke_bytes + pat.nnz * 8 + table_bytes
+    form = ctypes.c_int32()
+    _lib.check(_lib.lib().soptx_debug_general_path(pat._h, ctypes.byref(form)), "general_path")
+    moved = pat.nnz * 8
+    if form.value == 3:
+        moved += m.n_cells * 27 * 10 * 8
+    else:
+        nblk = pat.nnz // 9
+        moved += 2 * m.n_cells * 27 * 27 * 9 * 8 + 4 * (nblk + 1) + 4 * m.n_cells * 27 * 27 + 4 * nblk
     return {"mesh": "60x20x20 Q2 hexahedra (side 2), interior nodes jittered by 0.15", "elements": m.n_cells,
-            "ndof": pat.ndof, "nnz": pat.nnz, "avg_ms": avg * 1e3, "elements_per_s": m.n_cells / avg,
+            "form": {3: "by row groups (k_assemble_hex27)"}.get(
+                form.value, "element matrices through memory (k_ke_general_wide, k_gather_general)"),
+            "K_bytes": pat.nnz * 8, "K_write_GBs": pat.nnz * 8 / avg / 1e9, "ndof": pat.ndof, "nnz": pat.nnz, "avg_ms": avg * 1e3, "elements_per_s": m.n_cells / avg,
             "bytes_moved": moved, "effective_GBs": moved / avg / 1e9, "evaluate_avg_ms": ev_avg * 1e3,
             "step_elements_per_s": m.n_cells / (avg + ev_avg), "pattern_build_s": build_s}
 
