@@ -260,11 +260,12 @@ int soptx_build_pattern_general(const soptx_mesh *mesh, soptx_pattern *out, void
 /* SIMP stiffness assembly (Sec. 2.1, Sec. 2.2) with the element matrices
  * integrated by the element's Gauss rule with J evaluated at every quadrature
  * point (Q1 quadrilaterals and hexahedra, affine or not, and Q2 hexahedra),
- * FP64: each element's
- * blocks E(rho_e) sum_q w_q |det J_q| L(g_i g_j^T), g = J_q^-T grad(phi) the
- * physical gradients, are formed in a workspace (n_cells nen^2 DIM^2 doubles
- * per (device, stream), allocated on first use), then every CSR block sums
- * its contributions in ascending element order.  d_rho: [n_cells] double;
+ * FP64: block (i, j) of K sums its elements'
+ * E(rho_e) sum_q w_q |det J_q| L(g_i g_j^T), g = J_q^-T grad(phi) the
+ * physical gradients, in a fixed order.  The sums are formed on chip (Q1: on
+ * the plan's node groups, Q2: by row groups); on meshes whose plan does not
+ * fit that, the elements' blocks go through a workspace (n_cells nen^2 DIM^2
+ * doubles per (device, stream), allocated on first use).  d_rho: [n_cells] double;
  * d_dirichlet as in soptx_assemble (NULL: none); d_K_vals: [nnz].  Only for
  * handles of soptx_build_pattern_general (SOPTX_E_INVALID_ARG otherwise);
  * SOPTX_E_UNSUPPORTED_ELEM for simplices.  Asynchronous on stream. */
@@ -293,7 +294,10 @@ int soptx_evaluate_general(soptx_pattern h, const soptx_material *m, const doubl
  * for the recurrence residual, checked at the start and every 8 iterations,
  * or after max_iter iterations; *h_iters and *h_relres (host) give the count
  * and ||r_k|| / ||f|| (NaN after a breakdown, i.e. K not SPD).  A start
- * already within the tolerance returns after 0 iterations.  Synchronizes stream at those read-backs and at the start.  The
+ * already within the tolerance returns after 0 iterations.  Synchronizes
+ * stream at the start and at the end, and waits for a check's result in
+ * between (on small systems the checks run on the device and up to four more
+ * iterations are enqueued meanwhile; after a stop they change nothing).  The
  * vectors live in a per-stream workspace of the library. */
 int soptx_pcg(soptx_pattern h, const double *d_K_vals, const double *d_f, double *d_u, double rtol,
               int32_t max_iter, int32_t *h_iters, double *h_relres, void *stream);

@@ -2,7 +2,7 @@
 
 K(rho) = sum_e E(rho_e) K_e^0 is linear in E(rho_e), so for any loss L(K)
 dL/drho_e = E'(rho_e) <dL/dK, K_e^0> over the element's slots: the reverse of
-assembly, computed by the library's backward kernel (soptx_assemble_backward).
+assembly, computed by the library's backward kernels (Pattern.backward).
 With dL/dK = -u u^T restricted to the pattern this is the compliance
 sensitivity of Appendix D (dc_e = -E'(rho_e) u_e^T K_e^0 u_e); entries of
 fixed rows and columns are constants of the assembly and carry no gradient.

@@ -132,12 +132,13 @@ __device__ __forceinline__ int table(const int32_t *p, int64_t i) {
 // element): first terms, second terms, then any more from slots; and the rows
 // leave as whole runs by non-temporal stores.
 //
-// Measured on the curved 60 x 20 x 20 mesh: 535 us with its tables (110 MB)
-// and geometry in the last-level cache, 610 from HBM, against the 990 of the
-// element-matrix form (renumbered at random 569 against 996; 2,000 elements 66
-// against 95, 36 elements 16 against 18).  FP64 issue takes half the cycles (54 of 100 operations are
-// the products), LDS 56 %: with two waves per SIMD (256 VGPRs) neither is
-// reached.  On the way: three workgroups per CU with a slot for every further
+// Measured on the curved 60 x 20 x 20 mesh, back to back: 543 us on the same
+// inputs (tables and geometry, 109 MB, in the last-level cache), 602 with three
+// patterns in turn, against the 990 of the element-matrix form (renumbered at
+// random 569 against 996; 2,000 elements 66 against 95, 36 elements 16 against
+// 18); under the profiler 594 to 664.  Vector instructions take half the issue
+// cycles (58 of 100 are FMAs), LDS 57 %: with two waves per SIMD (256 VGPRs)
+// neither is reached.  On the way: three workgroups per CU with a slot for every further
 // term 690 us; the terms added rank by rank 585; 8-byte instead of 16-byte LDS
 // moves of the gradients 15 us more; four waves a workgroup sharing the points,
 // and persistent workgroups that read the next group's tables ahead, spill

@@ -1468,13 +1468,14 @@ __device__ __forceinline__ void point_wide(const AsmParams &P, const int *hdr, i
 // sum: the passes in order; in a pass, the lane's contributions in the
 // plan's order, each over the pass's points in order; then a split
 // position's halves, or a wide item's phases, as in k_assemble.
-// Bound by its vector instructions, of which one in four was an FMA of a
-// contribution: what does not change from pass to pass (a pairs item's lists,
-// the LDS entries of its first contributions; two fewer for the second item,
-// whose lists are shorter, as 128 registers hold four waves per SIMD) is found
-// once, an entry gives its addresses by two shifts, and the geometry is read
+// Bound by its vector instructions (53 % of issue, 36 of 100 of them FP64 FMAs,
+// LDS active 51 %) and the waits between a pass's two halves.  So what does not
+// change from pass to pass (a pairs item's lists, the LDS entries of its first
+// contributions; two fewer for the second item, whose lists are shorter, as 128
+// registers hold four waves per SIMD) is found once, an entry gives its addresses by two shifts, and the geometry is read
 // at a base of the wave with a 32-bit offset.  Jittered 120x40x40 hexahedra:
-// 198 us, against 226 with all of that found anew in every pass, and 241 with
+// 198 us (190 back to back on the same inputs, 213 with three patterns in turn),
+// against 226 with all of that found anew in every pass, and 241 with
 // the gradients read 8 bytes at a time (six LDS reads per contribution and point
 // instead of four) and the items dealt w, w + NW.
 template <int DIM>
